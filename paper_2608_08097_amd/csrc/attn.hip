@@ -51,16 +51,24 @@ constexpr int kMaxSplits = 16;
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// XCD-aware placement: workgroup ids are dealt round-robin over the 8 XCDs, so
-// the splits of one (request, KV head) are given ids that share id % 8 and
-// therefore one L2 (the query rows they all read stay local).
-__device__ __forceinline__ bool map_workgroup(int wg, int nrh, int nsplit, int& rh, int& split) {
-  const int xcd = wg & 7;
-  const int local = wg >> 3;
-  const int rh_local = local / nsplit;
-  split = local - rh_local * nsplit;
-  rh = rh_local * 8 + xcd;
-  return rh < nrh;
+// XCD-aware placement of the `parts` items of each (request, KV head) pair:
+// workgroup ids are dealt round-robin over the 8 XCDs, so id i works on item
+// (i % 8) * ceil(items / 8) + i / 8 and every XCD takes one contiguous run of
+// the items in pair order. The parts of a pair share query rows and partials
+// in one L2, the heads of a request, whose slots are adjacent in the pools,
+// share its XCD, and any number of pairs spreads over all XCDs. (Pairs dealt
+// modulo 8, as before: 90 requests x 8 KV heads, 761 MB, 143 against 124 us a
+// call; 64 x 8, 544 MB, 103 and 94 us.) With fewer than 8 pairs each takes an
+// XCD of its own, so that its merge reads the partials from the L2 that holds
+// them (1 pair: 9.3 us, spread over the XCDs 10.2). Returns -1 past the last item.
+__device__ __forceinline__ int xcd_item(int wg, int pairs, int parts) {
+  const int items = pairs * parts;
+  const int per = pairs < 8 ? parts : (items + 7) >> 3;
+  const int item = (wg & 7) * per + (wg >> 3);
+  return item < items ? item : -1;
+}
+inline unsigned xcd_grid(long long pairs, long long parts) {
+  return (unsigned)(pairs < 8 ? parts * 8 : (pairs * parts + 7) / 8 * 8);
 }
 
 // K and V registers of one 32-token unit (the operands of its MFMAs).
@@ -69,40 +77,53 @@ struct UnitRegs {
   u32x4 v[8];
 };
 
+// Byte offsets of a lane's operands inside a unit, from the unit's first slot:
+// with every unit address a wave-uniform base plus a 32-bit lane offset and a
+// constant, a load costs no 64-bit vector arithmetic. The second slot of a
+// B = 16 unit sits slot_bytes further (k1, v1); offsets k0, v0 stay in the first.
+struct UnitOffsets {
+  uint32_t k0, v0, k1, v1;
+};
+template <int BS>
+__device__ __forceinline__ UnitOffsets unit_offsets(long long slot_elems, int g, int i) {
+  UnitOffsets o;
+  // K: lane (g, i), token tile tau -> unit token 8*(i/4) + 4*tau + i%4 (the tile is in the constant part)
+  const uint32_t tok = 8 * (i >> 2) + (i & 3);
+  o.k0 = ((BS == 16 ? tok & 15 : tok) * kHeadDim + g * 8) * 2;
+  // V^T: lane (g, i), d-tile dt -> V[tokens 8g .. 8g+7][d = dt*16 + i]
+  o.v0 = (i * BS + (BS == 16 ? g & 1 : g) * 8) * 2;
+  const uint32_t slot_bytes = BS == 16 ? (uint32_t)slot_elems * 2 : 0;
+  o.k1 = o.k0 + (i >= 8 ? slot_bytes : 0);
+  o.v1 = o.v0 + (g >= 2 ? slot_bytes : 0);
+  return o;
+}
+
 // Unit u (wave-uniform) covers slots s0 = 2u, s1 = 2u + 1 at B = 16 or slot u
-// at B = 32. Every load is unconditional: a slot index past the pool is
-// clamped onto the local slot (always inside the pool) and only the token
-// counts n0 / n1 decide which tokens count. Free slots may hold anything,
-// even NaN; their K only yields masked scores and their V is cleared below.
+// at B = 32. Every load is unconditional: a second slot past the pool is
+// replaced by the first (always inside the pool) and only the token counts
+// n0 / n1 decide which tokens count. Free slots may hold anything, even NaN;
+// their K only yields masked scores and their V is cleared below.
 //
-// u < 0 is a placeholder unit: the loads are issued anyway (on the local slot,
-// which is cache-resident after its first read) and count nothing. Issuing
-// the same number of loads on every path keeps the compiler's wait counts
-// exact, so waiting for the current unit never drains the prefetched one.
+// u < 0 is a placeholder unit: the loads are issued anyway (every lane on the
+// first bytes of the local slot, one cache line) and count nothing. Issuing the
+// same number of loads on every path keeps the compiler's wait counts exact,
+// so waiting for the current unit never drains the prefetched one.
 template <int BS>
 __device__ __forceinline__ void load_unit(UnitRegs& ur, int u, int ks, const uint16_t* pk, const uint16_t* pv,
-                                          long long slot_elems, int g, int i) {
+                                          long long slot_elems, const UnitOffsets& o) {
   const bool real = u >= 0;
   const int s0 = real ? (BS == 16 ? 2 * u : u) : ks;
-  const int s1raw = real ? (BS == 16 ? 2 * u + 1 : ks + 1) : ks + 1;
-  const int s1 = s1raw <= ks ? s1raw : ks;
-  const uint16_t* k0 = pk + (long long)s0 * slot_elems;
-  const uint16_t* k1 = pk + (long long)s1 * slot_elems;
-  const uint16_t* v0 = pv + (long long)s0 * slot_elems;
-  const uint16_t* v1 = pv + (long long)s1 * slot_elems;
-  // K: lane (g, i), token tile tau -> unit token 8*(i/4) + 4*tau + i%4
+  const bool two = BS == 16 && s0 < ks;
+  const uint32_t ok = real ? (two ? o.k1 : o.k0) : 0u;
+  const uint32_t ov = real ? (two ? o.v1 : o.v0) : 0u;
+  const char* kb = reinterpret_cast<const char*>(pk + (long long)s0 * slot_elems);
+  const char* vb = reinterpret_cast<const char*>(pv + (long long)s0 * slot_elems);
 #pragma unroll
-  for (int tau = 0; tau < 2; ++tau) {
-    const int tok = 8 * (i >> 2) + 4 * tau + (i & 3);
-    const uint16_t* src = BS == 16 ? ((tok < 16 ? k0 : k1) + (tok & 15) * kHeadDim + g * 8)
-                                   : (k0 + tok * kHeadDim + g * 8);
+  for (int tau = 0; tau < 2; ++tau)
 #pragma unroll
-    for (int st = 0; st < 4; ++st) ur.k[tau][st] = ldg16(src + st * 32);
-  }
-  // V^T: lane (g, i), d-tile dt -> V[tokens 8g .. 8g+7][d = dt*16 + i]
-  const uint16_t* vsrc = BS == 16 ? ((g < 2 ? v0 : v1) + (g & 1) * 8) : (v0 + 8 * g);
+    for (int st = 0; st < 4; ++st) ur.k[tau][st] = ldg16(kb + ok + (tau * 4 * kHeadDim + st * 32) * 2);
 #pragma unroll
-  for (int dt = 0; dt < 8; ++dt) ur.v[dt] = ldg16(vsrc + (long long)(dt * 16 + i) * BS);
+  for (int dt = 0; dt < 8; ++dt) ur.v[dt] = ldg16(vb + ov + dt * 16 * BS * 2);
 }
 
 // Attended tokens of the two slots of unit u (u < 0: none): a slot below k_slots
@@ -240,7 +261,15 @@ __device__ __forceinline__ uint64_t map_mask(int ks, int slot, int entry) {
 }
 
 // Split kernel for one or two row tiles (up to 32 rows): K and V straight
-// into registers, every wave a strided subset of the split's units.
+// into registers, every wave a strided subset of the part's units.
+//
+// Units whose slots are all free are not read: the first two units of a wave
+// are loaded before the slot map has arrived, every later one is the next unit
+// with an attended slot. At 64 requests x 8 KV heads with contexts of 200 to
+// 3,000 tokens in 128-slot pools (383 of 541 MB attended) a call takes 74 us,
+// against 104 us when every slot is read. Every unit's addresses are a
+// wave-uniform base and a 32-bit lane offset (UnitOffsets); 64-bit vector
+// addresses took 17.9 against 16.9 us at 8 x 131,072 tokens (68 MB).
 template <int NT, int BS>
 __global__ __launch_bounds__(kW * 64) void attn_split_kernel(AttnArgs a) {
   static_assert(NT <= 2, "three or more row tiles take attn_split_rows_kernel");
@@ -248,17 +277,19 @@ __global__ __launch_bounds__(kW * 64) void attn_split_kernel(AttnArgs a) {
   const int lane = threadIdx.x & 63;
   const int g = lane >> 4;
   const int i = lane & 15;
-  const int nrh = a.R * a.Hkv;
-  int rh, split;
-  if (!map_workgroup(blockIdx.x, nrh, a.nsplit, rh, split)) return;
-  const int r = rh / a.Hkv;
-  const int h = rh - r * a.Hkv;
+  const int item = xcd_item(blockIdx.x, a.R * a.Hkv, a.nsplit);
+  if (item < 0) return;
   const int ks = a.k_slots;
   const long long slot_elems = (long long)a.Hkv * BS * kHeadDim;
-  const long long head_off = (long long)h * BS * kHeadDim;
-  const uint16_t* pk = a.pool_k + (long long)r * (ks + 1) * slot_elems + head_off;
-  const uint16_t* pv = a.pool_v + (long long)r * (ks + 1) * slot_elems + head_off;
+  const int rh = item / a.nsplit;
+  const int split = item - rh * a.nsplit;
+  const int r = rh / a.Hkv;
+  const int h = rh - r * a.Hkv;
+  const long long pool_off = (long long)r * (ks + 1) * slot_elems + (long long)h * BS * kHeadDim;
+  const uint16_t* pk = a.pool_k + pool_off;
+  const uint16_t* pv = a.pool_v + pool_off;
   const int32_t* smap = a.slot_map + (long long)rh * ks;
+  const UnitOffsets uo = unit_offsets<BS>(slot_elems, g, i);
   const int u_begin = split * a.units_per_split;
   const int u_end = min(a.n_units, u_begin + a.units_per_split);
   // unit t of this wave is u_first + t * kW, t < nt
@@ -266,13 +297,12 @@ __global__ __launch_bounds__(kW * 64) void attn_split_kernel(AttnArgs a) {
   const int nt = u_first < u_end ? (u_end - u_first + kW - 1) / kW : 0;
   auto unit = [&](int t) { return t < nt ? u_first + t * kW : -1; };
   constexpr int kChunk = BS == 16 ? 32 : 64;  // units per validity mask
-  auto bit_of = [&](int t) { return BS == 16 ? 2 * (t & (kChunk - 1)) : (t & (kChunk - 1)); };
 
   // The first unit's loads go out before anything else, so that no wave starts
   // by waiting for a scalar or query load; the queries, the slot map and the
   // context length follow.
   UnitRegs ua, ub;
-  load_unit<BS>(ua, unit(0), ks, pk, pv, slot_elems, g, i);
+  load_unit<BS>(ua, unit(0), ks, pk, pv, slot_elems, uo);
 
   // Q^T operand: lane (g, i) holds row v*16 + i of tile v, dims st*32 + 8g .. +8.
   bf16x8 qb[NT][4];
@@ -290,12 +320,13 @@ __global__ __launch_bounds__(kW * 64) void attn_split_kernel(AttnArgs a) {
       for (int st = 0; st < 4; ++st) qb[v][st] = as_bf16x8(u32x4{0, 0, 0, 0});
     }
   }
-  const int map_slot = unit_slot<BS>(u_first, 0, lane);
-  int map_entry = map_load(smap, ks, map_slot, a.ctx_len + r);
+  int map_entry = map_load(smap, ks, unit_slot<BS>(u_first, 0, lane), a.ctx_len + r);
   // a vector load (relaxed atomic) whose value is pinned to a VGPR until the
   // next unit's loads are out, so that the wait for it comes after them
   int ctx_raw = __hip_atomic_load(a.ctx_len + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   __builtin_amdgcn_sched_barrier(0);
+  load_unit<BS>(ub, unit(1), ks, pk, pv, slot_elems, uo);
+  __builtin_amdgcn_sched_barrier(0);  // both units' loads are issued before the first wait
 
   float m_run[NT], l_run[NT];  // row reference maximum (log2 units) and this lane's partial sum
   f32x4 acc[NT][8];
@@ -307,17 +338,44 @@ __global__ __launch_bounds__(kW * 64) void attn_split_kernel(AttnArgs a) {
     for (int dt = 0; dt < 8; ++dt) acc[v][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
 
-  int local_len = 0;
-  // One unit: counts from the mask (reloaded at the first unit of every chunk
-  // after the first), V of unattended tokens cleared, then the online softmax.
-  uint64_t vmask = 0;
-  auto run = [&](UnitRegs& cur, int t) {
-    if (t > 0 && (t & (kChunk - 1)) == 0) {
+  // the map entries and the context length are in
+  asm volatile("" : "+v"(map_entry), "+v"(ctx_raw));
+  const int local_len = ctx_blocks(__builtin_amdgcn_readfirstlane(ctx_raw), BS, a.NBmax).local_len;
+  int chunk = 0;
+  uint64_t vmask = map_mask(ks, unit_slot<BS>(u_first, 0, lane), map_entry);
+  // Units of the current chunk with an attended slot, one bit each at the
+  // position of their first slot in vmask; the unit of the local block counts.
+  auto live_units = [&]() {
+    uint64_t m = BS == 16 ? (vmask | (vmask >> 1)) & 0x5555555555555555ull : vmask;
+    const int tl = a.n_units - 1 - u_first;  // t of the local unit, times kW
+    if (tl >= 0 && tl % kW == 0) {
+      const int t = tl / kW - chunk * kChunk;
+      if (t >= 0 && t < kChunk) m |= 1ull << (BS == 16 ? 2 * t : t);
+    }
+    return m;
+  };
+  uint64_t live = live_units();
+  // The next unit of this wave after t to attend (nt: none): the next one of its
+  // chunk with an attended slot, or the chunk's last one (which then counts no
+  // token); a new chunk's map is read when its first unit is reached.
+  auto next_unit = [&](int t) __attribute__((always_inline)) {
+    ++t;
+    if ((t & (kChunk - 1)) == 0 && t < nt) {
+      chunk = t / kChunk;
       const int slot = unit_slot<BS>(u_first, t, lane);
       vmask = map_mask(ks, slot, map_load(smap, ks, slot, a.ctx_len + r));
+      live = live_units();
     }
-    int n0, n1;
-    unit_counts<BS>(unit(t), ks, local_len, vmask, bit_of(t), n0, n1);
+    const int p = t & (kChunk - 1);
+    const uint64_t rest = live >> (BS == 16 ? 2 * p : p) | 1ull << (BS == 16 ? 2 * (kChunk - 1 - p) : kChunk - 1 - p);
+    return min(nt, t + (BS == 16 ? __builtin_ctzll(rest) / 2 : __builtin_ctzll(rest)));
+  };
+  // attended tokens of the slots of unit t, from the current chunk's mask
+  auto counts = [&](int t, int& n0, int& n1) __attribute__((always_inline)) {
+    unit_counts<BS>(unit(t), ks, local_len, vmask, BS == 16 ? 2 * (t & (kChunk - 1)) : (t & (kChunk - 1)), n0, n1);
+  };
+  // One unit: V of unattended tokens cleared, then the online softmax.
+  auto run = [&](UnitRegs& cur, int n0, int n1) __attribute__((always_inline)) {
     const int keep = lane_keep<BS>(n0, n1, g);
     const bool partial = __builtin_amdgcn_ballot_w64(keep < 8) != 0;
     if (partial) mask_unit_v(cur, keep);
@@ -328,21 +386,20 @@ __global__ __launch_bounds__(kW * 64) void attn_split_kernel(AttnArgs a) {
   // (one exposed memory latency per wave, not per unit). Loads past the wave's
   // last unit are placeholders on the local slot (cache-resident), so the
   // compiler's wait counts stay exact.
-  auto settle = [&]() {  // the map entries and the context length are in
-    asm volatile("" : "+v"(map_entry), "+v"(ctx_raw));
-    vmask = map_mask(ks, map_slot, map_entry);
-    local_len = ctx_blocks(ctx_raw, BS, a.NBmax).local_len;
-  };
-  load_unit<BS>(ub, unit(1), ks, pk, pv, slot_elems, g, i);
-  __builtin_amdgcn_sched_barrier(0);  // both units' loads are issued before the first wait
-  settle();
-  for (int t = 0; t < nt;) {
-    run(ua, t);
-    if (++t >= nt) break;
-    load_unit<BS>(ua, unit(t + 1), ks, pk, pv, slot_elems, g, i);
-    run(ub, t);
-    if (++t >= nt) break;
-    load_unit<BS>(ub, unit(t + 1), ks, pk, pv, slot_elems, g, i);
+  int ta = 0, tb = 1, na0, na1, nb0, nb1;
+  counts(0, na0, na1);
+  counts(1, nb0, nb1);
+  if (nt > 0) for (;;) {
+    run(ua, na0, na1);
+    if (tb >= nt) break;
+    ta = next_unit(tb);
+    load_unit<BS>(ua, unit(ta), ks, pk, pv, slot_elems, uo);
+    counts(ta, na0, na1);
+    run(ub, nb0, nb1);
+    tb = next_unit(ta);
+    load_unit<BS>(ub, unit(tb), ks, pk, pv, slot_elems, uo);
+    counts(tb, nb0, nb1);
+    if (ta >= nt) break;
   }
   // row sums: add the partial sums of the four lanes of every row
 #pragma unroll
@@ -621,9 +678,10 @@ __global__ __launch_bounds__(NT * 64) void attn_split_rows_kernel(AttnArgs a) {
   const int lane = threadIdx.x & 63;
   const int g = lane >> 4;
   const int i = lane & 15;
-  const int nrh = a.R * a.Hkv;
-  int rh, split;
-  if (!map_workgroup(blockIdx.x, nrh, a.nsplit, rh, split)) return;
+  const int item = xcd_item(blockIdx.x, a.R * a.Hkv, a.nsplit);
+  if (item < 0) return;
+  const int rh = item / a.nsplit;
+  const int split = item - rh * a.nsplit;
   const int r = rh / a.Hkv;
   const int h = rh - r * a.Hkv;
   const int ks = a.k_slots;
@@ -761,22 +819,17 @@ __global__ __launch_bounds__(NT * 64) void attn_split_rows_kernel(AttnArgs a) {
 // Merge of the NS splits: a workgroup takes kMergeRows rows of one (request,
 // KV head), 32 threads a row, each thread 4 dimensions; every thread issues its
 // NS partial loads (16 bytes each) and the row's NS (max, sum) pairs at once.
-// Workgroup ids are dealt so that the head's id % 8, which places its splits on
-// one XCD, places its merge there too: the partials are read from the L2 that
-// holds them.
+// The items are dealt over the XCDs as the splits are (xcd_item, pairs in
+// order), so most partials are read from the L2 that holds them.
 constexpr int kMergeRows = 8;
 
 template <int NS>
 __global__ __launch_bounds__(kMergeRows * 32) void attn_merge_kernel(AttnArgs a) {
-  const int nrh = a.R * a.Hkv;
   const int groups = (a.rows + kMergeRows - 1) / kMergeRows;
-  const int wg = blockIdx.x;
-  const int local = wg >> 3;
-  const int rh_local = local / groups;
-  const int grp = local - rh_local * groups;
-  const int rh = rh_local * 8 + (wg & 7);
-  const int row = grp * kMergeRows + (threadIdx.x >> 5);
-  if (rh >= nrh || row >= a.rows) return;
+  const int item = xcd_item(blockIdx.x, a.R * a.Hkv, groups);
+  const int rh = item / groups;
+  const int row = (item - rh * groups) * kMergeRows + (threadIdx.x >> 5);
+  if (item < 0 || row >= a.rows) return;
   const int c4 = threadIdx.x & 31;
   const int r = rh / a.Hkv;
   const int h = rh - r * a.Hkv;
@@ -815,46 +868,45 @@ __global__ __launch_bounds__(kMergeRows * 32) void attn_merge_kernel(AttnArgs a)
 }
 
 template <int NS>
-void launch_merge_ns(const AttnArgs& a, hipStream_t s, const LaunchTiming& t, int nrh8) {
-  const int groups = (a.rows + kMergeRows - 1) / kMergeRows;
-  launch_kernel(attn_merge_kernel<NS>, dim3((unsigned)(nrh8 * groups)), dim3(kMergeRows * 32), s, t, a);
+void launch_merge_ns(const AttnArgs& a, hipStream_t s, const LaunchTiming& t) {
+  const long long groups = (a.rows + kMergeRows - 1) / kMergeRows;
+  launch_kernel(attn_merge_kernel<NS>, dim3(xcd_grid(a.R * a.Hkv, groups)), dim3(kMergeRows * 32), s, t, a);
 }
 
-void launch_merge(const AttnArgs& a, hipStream_t s, const LaunchTiming& t, int nrh8) {
+void launch_merge(const AttnArgs& a, hipStream_t s, const LaunchTiming& t) {
   switch (a.nsplit) {
-    case 2: return launch_merge_ns<2>(a, s, t, nrh8);
-    case 3: return launch_merge_ns<3>(a, s, t, nrh8);
-    case 4: return launch_merge_ns<4>(a, s, t, nrh8);
-    case 5: return launch_merge_ns<5>(a, s, t, nrh8);
-    case 6: return launch_merge_ns<6>(a, s, t, nrh8);
-    case 7: return launch_merge_ns<7>(a, s, t, nrh8);
-    case 8: return launch_merge_ns<8>(a, s, t, nrh8);
-    case 9: return launch_merge_ns<9>(a, s, t, nrh8);
-    case 10: return launch_merge_ns<10>(a, s, t, nrh8);
-    case 11: return launch_merge_ns<11>(a, s, t, nrh8);
-    case 12: return launch_merge_ns<12>(a, s, t, nrh8);
-    case 13: return launch_merge_ns<13>(a, s, t, nrh8);
-    case 14: return launch_merge_ns<14>(a, s, t, nrh8);
-    case 15: return launch_merge_ns<15>(a, s, t, nrh8);
-    default: return launch_merge_ns<kMaxSplits>(a, s, t, nrh8);
+    case 2: return launch_merge_ns<2>(a, s, t);
+    case 3: return launch_merge_ns<3>(a, s, t);
+    case 4: return launch_merge_ns<4>(a, s, t);
+    case 5: return launch_merge_ns<5>(a, s, t);
+    case 6: return launch_merge_ns<6>(a, s, t);
+    case 7: return launch_merge_ns<7>(a, s, t);
+    case 8: return launch_merge_ns<8>(a, s, t);
+    case 9: return launch_merge_ns<9>(a, s, t);
+    case 10: return launch_merge_ns<10>(a, s, t);
+    case 11: return launch_merge_ns<11>(a, s, t);
+    case 12: return launch_merge_ns<12>(a, s, t);
+    case 13: return launch_merge_ns<13>(a, s, t);
+    case 14: return launch_merge_ns<14>(a, s, t);
+    case 15: return launch_merge_ns<15>(a, s, t);
+    default: return launch_merge_ns<kMaxSplits>(a, s, t);
   }
 }
 
 template <int NT, int BS>
 hipError_t launch_t(const AttnArgs& a, hipStream_t s, const LaunchTiming& t) {
-  const int nrh = a.R * a.Hkv;
-  const int nrh8 = (nrh + 7) / 8 * 8;
+  const long long nrh = (long long)a.R * a.Hkv;
   const bool merge = a.nsplit > 1;
   // timed as one span: from the split kernel's start to the merge kernel's end
   if constexpr (NT >= 3)
-    launch_kernel(attn_split_rows_kernel<NT, BS>, dim3((unsigned)(nrh8 * a.nsplit)), dim3(NT * 64), s,
+    launch_kernel(attn_split_rows_kernel<NT, BS>, dim3(xcd_grid(nrh, a.nsplit)), dim3(NT * 64), s,
                   LaunchTiming{t.start, merge ? nullptr : t.stop}, a);
   else
-    launch_kernel(attn_split_kernel<NT, BS>, dim3((unsigned)(nrh8 * a.nsplit)), dim3(kW * 64), s,
+    launch_kernel(attn_split_kernel<NT, BS>, dim3(xcd_grid(nrh, a.nsplit)), dim3(kW * 64), s,
                   LaunchTiming{t.start, merge ? nullptr : t.stop}, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !merge) return e;
-  launch_merge(a, s, LaunchTiming{nullptr, t.stop}, nrh8);
+  launch_merge(a, s, LaunchTiming{nullptr, t.stop});
   return hipGetLastError();
 }
 
@@ -878,17 +930,33 @@ AttnPlan attn_plan(int R, int Hq, int Hkv, int T, int B, int k_slots) {
   p.rows = G * T;
   p.n_units = B == 16 ? (k_slots + 2) / 2 : k_slots + 1;
   const long long nrh = (long long)R * Hkv;
+  // `want` splits of at least `least` units each, at most kMaxSplits
+  auto split = [&](long long want, int least) {
+    const long long most = (p.n_units + least - 1) / least;
+    want = want < most ? want : most;
+    want = want < kMaxSplits ? want : kMaxSplits;
+    want = want > 1 ? want : 1;
+    p.units_per_split = (int)((p.n_units + want - 1) / want);
+    p.nsplit = (p.n_units + p.units_per_split - 1) / p.units_per_split;
+  };
+  // The workspace holds the partials of the smallest split that gives every CU
+  // a workgroup and every wave a unit, the finest split that can pay.
   long long want = (kTargetWorkgroups + nrh - 1) / (nrh > 0 ? nrh : 1);
-  const long long most = (p.n_units + kW - 1) / kW;  // at least one unit per wave
-  if (want > most) want = most;
-  if (want > kMaxSplits) want = kMaxSplits;
-  if (want < 1) want = 1;
-  p.units_per_split = (int)((p.n_units + want - 1) / want);
-  p.nsplit = (p.n_units + p.units_per_split - 1) / p.units_per_split;
+  split(want, kW);
+  p.bytes = p.nsplit > 1 ? (size_t)nrh * p.nsplit * p.rows * (kHeadDim + 2) * sizeof(float) : 0;
+  // The split launched is the largest that needs no second round of workgroups:
+  // a CU holds one workgroup (of up to two row tiles: one wave per SIMD), so a
+  // few workgroups more than CUs take a round of their own. Measured on MI355X
+  // (8 KV heads, 20 rows, budget 2,048), smallest split that fills against this
+  // one: 3 requests 17.3 against 12.8 us, 5 requests 18.1 and 13.0, 17 requests
+  // 43.0 and 33.6, 22 requests (two splits against one, no merge) 46.3 and 35.5.
+  if (p.nsplit > 1 && nrh * p.nsplit > kTargetWorkgroups) want = kTargetWorkgroups / nrh;
+  // With more than 16 rows to merge, a few units more per split and fewer splits
+  // (1 request x 8 KV heads, 20 rows: 13 splits of 5 units 10.8 us, 11 of 6 10.4
+  // us; 8 rows: 8.3 us either way).
+  split(want, p.rows <= 16 ? kW : 6);
   // partials exist only with several splits (one split writes the outputs itself)
   p.part_o_floats = p.nsplit > 1 ? (size_t)nrh * p.nsplit * p.rows * kHeadDim : 0;
-  p.part_ml_floats = p.nsplit > 1 ? (size_t)nrh * p.nsplit * p.rows * 2 : 0;
-  p.bytes = (p.part_o_floats + p.part_ml_floats) * sizeof(float);
   return p;
 }
 

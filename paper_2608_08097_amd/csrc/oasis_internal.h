@@ -216,7 +216,7 @@ struct AttnArgs {
 };
 struct AttnPlan {
   int rows, n_units, nsplit, units_per_split;
-  size_t part_o_floats, part_ml_floats, bytes;
+  size_t part_o_floats, bytes;  // bytes: what oasis_attn_workspace_bytes returns
 };
 AttnPlan attn_plan(int R, int Hq, int Hkv, int T, int B, int k_slots);
 hipError_t launch_attn(const AttnArgs& a, hipStream_t s, const LaunchTiming& t = {});
