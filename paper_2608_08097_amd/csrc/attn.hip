@@ -32,10 +32,9 @@
 //
 // With more than two row tiles (G * T > 32 rows) the registers of one wave no
 // longer hold every tile's accumulators next to two units of K and V; there a
-// workgroup has one wave per row tile and the unit's K and V cross HBM once,
+// workgroup has two waves per row tile and the unit's K and V cross HBM once,
 // into LDS, for all of them (attn_split_rows_kernel).
 #include <mutex>
-#include <utility>
 
 #include "oasis_internal.h"
 
@@ -45,7 +44,7 @@ namespace {
 constexpr int kW = 4;  // waves per workgroup
 // Workgroups of one attention call: one per CU (the register-prefetching
 // kernel of up to two row tiles holds one wave per SIMD; the many-row kernel
-// one workgroup of up to five waves per CU).
+// one workgroup of up to ten waves per CU).
 constexpr int kTargetWorkgroups = 256;
 constexpr int kMaxSplits = 16;
 
@@ -489,74 +488,50 @@ __global__ __launch_bounds__(kW * 64) void attn_split_kernel(AttnArgs a) {
   }
 }
 
-// Split kernel for many row tiles (NT >= 3: G * T > 32 rows). A workgroup has
-// one wave per row tile; every wave attends its 16 rows to every unit of the
-// split, so the waves never merge softmax states and each writes its own rows.
-// Each unit's K and V cross HBM once: its 16 chunks (8 of K, 8 of V, 16 bytes
-// a lane, in the MFMA operand layout of load_unit) are loaded straight into
-// LDS, dealt round-robin to the waves, and every wave reads all 16 back as
-// conflict-free 16-byte LDS reads. A ring of kRowsStages units keeps
-// kRowsStages - 1 units in flight; one barrier per unit publishes a unit to
-// every wave and frees the stage of the one before.
+// Split kernel for many row tiles (NT >= 3: G * T > 32 rows). Each unit's K and
+// V cross HBM once: its 16 chunks (8 of K, 8 of V, 16 bytes a lane, in the MFMA
+// operand layout of load_unit) are loaded straight into LDS, and one wave per
+// row tile reads all 16 back as conflict-free 16-byte LDS reads. A workgroup
+// has two such teams of waves, on alternate units: with one team (3 to 5 waves)
+// a unit's chain of LDS reads, score products, softmax and PV products paces
+// the loads, since a SIMD then has one wave, or none, to issue from. A step
+// holds one unit per team; a ring of kRowsStages steps keeps kRowsStages - 1 in
+// flight; one barrier per step publishes it to every wave and frees the stage
+// of the one before. The teams' softmax states are merged through LDS at the
+// end, so that the workgroup still leaves one partial per row.
 //
-// Measured on MI355X (16 requests x 8 KV heads x 72 rows, B = 32, 4,096
-// tokens per head, 268 MB): 81.7 us for the register kernel (every wave loads
-// the units of its own split range, five row tiles per wave), 63 to 66 us here
-// with the merge and four stages; 1 to 2 us less with each unit's score
-// products issued one step ahead of its softmax and PV products (below),
-// about 1 us less again with the prologue's own loads on the DMA path
-// (below), and 0.5 to 1.5 us less again with three stages instead of four
-// (two: 80 us; six: no gain). Registers staged through VGPRs instead of
-// direct-to-LDS loads, two units ahead: 67 to 70 us; two workgroups per CU: no
-// gain; exact per-wave load counts instead of the surplus loads: 1 us slower.
+// Measured on MI355X, per call: 22 requests x 8 KV heads at 20,000 tokens, 72
+// rows (B = 16, 2,048-token budget, 189 MB) 68 us with one team, 45 us with two;
+// 25 requests at B = 32 and budget 4,096 (429 MB) 109 and 83 us; 16 x 65,536
+// tokens (B = 32, 72 rows, 274 MB; two splits per head and a merge) 63 and
+// 61 us. Three or four teams (two stages fit) 62.9 us at the last, four stages
+// 62.0, two 63.7. Each team's operands of a unit are read together and then
+// used: reading a K chunk, waiting and reading the next took 47 us at the first.
+// Short splits pay for the second team's part of the merge: 16 pairs in 15
+// splits of 9 units 17.4 us, one team 16.3.
+constexpr int kTeams = 2;
 constexpr int kRowsStages = 3;
-typedef u32x4 UnitLds[17][64];  // [chunk][lane]; chunk 16 takes the surplus loads
-
-template <int BS>
-__device__ __forceinline__ const uint16_t* chunk_src(int u, int j, int ks, const uint16_t* pk, const uint16_t* pv,
-                                                     long long slot_elems, int g, int i) {
-  // lane (g, i)'s 16 bytes of chunk j of unit u: j < 8 is K token tile tau = j / 4 at
-  // k-step st = j % 4, j >= 8 is V d-tile j - 8 (the addresses load_unit reads)
-  const bool real = u >= 0;
-  const int s0 = real ? (BS == 16 ? 2 * u : u) : ks;
-  const int s1raw = real ? (BS == 16 ? 2 * u + 1 : ks + 1) : ks + 1;
-  const int s1 = s1raw <= ks ? s1raw : ks;
-  if (j < 8) {
-    const int tau = j >> 2, st = j & 3;
-    const int tok = 8 * (i >> 2) + 4 * tau + (i & 3);
-    const uint16_t* k0 = pk + (long long)s0 * slot_elems;
-    const uint16_t* k1 = pk + (long long)s1 * slot_elems;
-    const uint16_t* src = BS == 16 ? ((tok < 16 ? k0 : k1) + (tok & 15) * kHeadDim + g * 8)
-                                   : (k0 + tok * kHeadDim + g * 8);
-    return src + st * 32;
-  }
-  const int dt = j - 8;
-  const uint16_t* v0 = pv + (long long)s0 * slot_elems;
-  const uint16_t* v1 = pv + (long long)s1 * slot_elems;
-  const uint16_t* vsrc = BS == 16 ? ((g < 2 ? v0 : v1) + (g & 1) * 8) : (v0 + 8 * g);
-  return vsrc + (long long)(dt * 16 + i) * BS;
-}
-
-// 16 bytes a lane from global memory straight into LDS (global_load_lds_dwordx4):
-// lane L's bytes land at lds_row + 16 L, lds_row being the same in every lane.
+// 16 bytes a lane from global memory (base + offset, base wave-uniform) straight
+// into LDS (global_load_lds_dwordx4): lane L's bytes land at lds_row + 16 L,
+// lds_row being the same in every lane.
 // Written as inline assembly because the compiler, which cannot tell the ring's
 // stages apart once they are reused, would otherwise wait for every earlier
 // such load before each one (a full drain per unit); the waits are the
 // explicit vmcnt counts of the kernel instead. The "memory" clobber keeps LDS
 // reads and writes in program order around it, and M0 (the LDS base operand
 // of the load) is restored after it.
-__device__ __forceinline__ void lds_dma16(const void* gsrc, void* lds_row) {
+__device__ __forceinline__ void lds_dma16(const void* base, uint32_t offset, void* lds_row) {
   const uint32_t lds =
       __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds_row);
   uint32_t saved;
   asm volatile(
       "s_mov_b32 %0, m0\n\t"
-      "s_mov_b32 m0, %2\n\t"
+      "s_mov_b32 m0, %3\n\t"
       "s_nop 0\n\t"
-      "global_load_lds_dwordx4 %1, off\n\t"
+      "global_load_lds_dwordx4 %1, %2\n\t"
       "s_mov_b32 m0, %0"
       : "=&s"(saved)
-      : "v"(gsrc), "s"(lds)
+      : "v"(offset), "s"(base), "s"(lds)
       : "memory");
 }
 
@@ -583,40 +558,17 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
 }
 
-// f(std::integral_constant<int, 0>{}), ..., f(std::integral_constant<int, N - 1>{})
-template <typename F, int... S>
-__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, S...>) {
-  (f(std::integral_constant<int, S>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  static_for_impl(f, std::make_integer_sequence<int, N>{});
-}
-
-// One 32-token unit of one row tile in two halves, so that a wave can issue
-// the next unit's score products before this unit's softmax and PV products
-// (software pipelining across units): unit_scores gives S^T of the unit
-// (lane (g, i): row i against unit tokens 8g .. 8g+7, as in process_unit);
-// unit_softmax_pv is the rest of process_unit for one row tile.
-__device__ __forceinline__ void unit_scores(const UnitRegs& cur, const bf16x8 (&qb)[4], f32x4 (&sc)[2]) {
+// Online softmax and PV products of one 32-token unit of one row tile, as in
+// process_unit; the V operands are read by `load_v` once the scores are known.
+template <typename LoadV>
+__device__ __forceinline__ void unit_softmax_pv(const f32x4 (&sc)[2], int keep, bool partial, float& m_ref,
+                                                float& l_part, f32x4 (&acc)[8], float scale_log2, LoadV&& load_v) {
+  u32x4 v[8];
 #pragma unroll
-  for (int tau = 0; tau < 2; ++tau) {
-    f32x4 s4 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int st = 0; st < 4; ++st)
-      s4 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(cur.k[tau][st]), qb[st], s4, 0, 0, 0);
-    sc[tau] = s4;
-  }
-}
-
-__device__ __forceinline__ void unit_softmax_pv(const f32x4 (&sc)[2], const u32x4 (&vin)[8], int keep, bool partial,
-                                                float& m_ref, float& l_part, f32x4 (&acc)[8], float scale_log2) {
+  for (int dt = 0; dt < 8; ++dt) v[dt] = load_v(dt);
   float x[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) x[e] = sc[e >> 2][e & 3] * scale_log2;
-  u32x4 v[8];
-#pragma unroll
-  for (int dt = 0; dt < 8; ++dt) v[dt] = vin[dt];
   if (partial) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) x[e] = e < keep ? x[e] : -INFINITY;
@@ -656,25 +608,18 @@ __device__ __forceinline__ void unit_softmax_pv(const f32x4 (&sc)[2], const u32x
 }
 
 template <int NT, int BS>
-__global__ __launch_bounds__(NT * 64) void attn_split_rows_kernel(AttnArgs a) {
-  static_assert(kRowsStages == 3, "one LDS variable per stage below");
-  constexpr int kPer = (16 + NT - 1) / NT;  // chunk loads per wave and unit
-  // One LDS variable per stage, always named with a compile-time stage, so the
-  // compiler sees each read of a stage apart from the other stages' loads.
-  // Every wave issues kPer loads a unit (the surplus ones re-read chunk 0 into
-  // row 16), so that one vmcnt count fits every wave.
-  __shared__ __align__(16) UnitLds s_st0;
-  __shared__ __align__(16) UnitLds s_st1;
-  __shared__ __align__(16) UnitLds s_st2;
-  __shared__ __align__(16) u32x4 s_q[NT][4][64];  // each wave's query operand (4 k-steps)
-  __shared__ int s_misc[NT][3][64];               // each wave's context length and two mask chunks
-  auto stage_buf = [&](auto S) __attribute__((always_inline)) -> UnitLds& {
-    constexpr int k = decltype(S)::value;
-    if constexpr (k == 0) return s_st0;
-    else if constexpr (k == 1) return s_st1;
-    else return s_st2;
-  };
-  const int v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // this wave's row tile
+__global__ __launch_bounds__(NT * kTeams * 64) void attn_split_rows_kernel(AttnArgs a) {
+  constexpr int kWaves = NT * kTeams;
+  constexpr int kPer = (16 + NT - 1) / NT;  // chunk loads per wave and step
+  constexpr int kLook = kRowsStages - 1;    // steps in flight
+  // ring of kRowsStages steps: [team][chunk][lane]; the surplus loads of every step share one row
+  __shared__ __align__(16) u32x4 s_ring[kRowsStages][kTeams][16][64];
+  __shared__ __align__(16) u32x4 s_junk[64];
+  __shared__ __align__(16) u32x4 s_q[NT][4][64];  // the row tiles' query operands (4 k-steps)
+  __shared__ int s_misc[kWaves][3][64];           // each wave's context length and two map chunks
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int team = wave / NT;       // takes every kTeams-th unit
+  const int v = wave - team * NT;   // this wave's row tile
   const int lane = threadIdx.x & 63;
   const int g = lane >> 4;
   const int i = lane & 15;
@@ -686,134 +631,180 @@ __global__ __launch_bounds__(NT * 64) void attn_split_rows_kernel(AttnArgs a) {
   const int h = rh - r * a.Hkv;
   const int ks = a.k_slots;
   const long long slot_elems = (long long)a.Hkv * BS * kHeadDim;
-  const long long head_off = (long long)h * BS * kHeadDim;
-  const uint16_t* pk = a.pool_k + (long long)r * (ks + 1) * slot_elems + head_off;
-  const uint16_t* pv = a.pool_v + (long long)r * (ks + 1) * slot_elems + head_off;
+  const long long pool_off = (long long)r * (ks + 1) * slot_elems + (long long)h * BS * kHeadDim;
+  const uint16_t* pk = a.pool_k + pool_off;
+  const uint16_t* pv = a.pool_v + pool_off;
   const int32_t* smap = a.slot_map + (long long)rh * ks;
+  const UnitOffsets uo = unit_offsets<BS>(slot_elems, g, i);
   const int u_begin = split * a.units_per_split;
   const int u_end = min(a.n_units, u_begin + a.units_per_split);
-  const int nt = u_end > u_begin ? u_end - u_begin : 0;  // units of this workgroup, in order
-  auto unit = [&](int t) __attribute__((always_inline)) { return t < nt ? u_begin + t : -1; };
 
-  // this wave's chunk loads of unit t into stage S (past the last unit: the placeholder slot)
-  auto issue = [&](int t, auto S) __attribute__((always_inline)) {
-    UnitLds& buf = stage_buf(S);
-    const int u = unit(t);
+  // This wave's chunk loads of its team's unit u into ring stage st (u < 0, past
+  // the last unit: every lane on the first bytes of the local slot, one cache
+  // line). Chunk j < 8 is K token tile j / 4 at k-step j % 4, j >= 8 V d-tile
+  // j - 8, in the MFMA operand layout of load_unit.
+  auto issue = [&](int u, int st) __attribute__((always_inline)) {
+    const bool real = u >= 0;
+    const int s0 = real ? (BS == 16 ? 2 * u : u) : ks;
+    const bool two = BS == 16 && s0 < ks;
+    const long long slot = (long long)s0 * slot_elems;
 #pragma unroll
     for (int c = 0; c < kPer; ++c) {
       const int j = v + c * NT;
-      lds_dma16(chunk_src<BS>(u, j < 16 ? j : 0, ks, pk, pv, slot_elems, g, i), &buf[j < 16 ? j : 16][0]);
+      const bool is_k = j < 8;
+      const uint32_t off = is_k ? (two ? uo.k1 : uo.k0) : (two ? uo.v1 : uo.v0);
+      const uint16_t* base = (is_k ? pk : pv) + slot +
+                             (is_k ? (j >> 2) * 4 * kHeadDim + (j & 3) * 32 : j < 16 ? (j - 8) * 16 * BS : 0);
+      lds_dma16(base, real && j < 16 ? off : 0u, j < 16 ? &s_ring[st][team][j][0] : &s_junk[0]);
     }
   };
-  // validity mask of units t .. t + kChunkU - 1 (lane l: map entry of slot l % 2 of
-  // unit t + l / 2 at B = 16, of unit t + l at B = 32)
-  constexpr int kChunkU = BS == 16 ? 32 : 64;
-  auto mask_slot = [&](int t) __attribute__((always_inline)) {
-    const int jj = BS == 16 ? lane >> 1 : lane;
-    return BS == 16 ? 2 * (u_begin + t + jj) + (lane & 1) : u_begin + t + jj;
+  // validity mask chunks: units ch * kChunk .. of the split (lane l: map entry of
+  // slot l % 2 of unit l / 2 at B = 16, of unit l at B = 32)
+  constexpr int kChunk = BS == 16 ? 32 : 64;
+  auto mask_slot = [&](int ch) __attribute__((always_inline)) {
+    const int u = u_begin + ch * kChunk;
+    return BS == 16 ? 2 * u + lane : u + lane;
   };
   // Everything else the unit loop reads (the context length, the slot-map
-  // entries of the first two mask chunks, this wave's query operand) takes the
-  // same LDS-DMA path, ahead of the ring's first units: the compiler cannot
-  // count the DMA loads, so its wait for any load it issues after them would
-  // drain the ring. Rows past the end load row 0's queries and are zeroed.
+  // entries of the first two mask chunks, the query operands) takes the same
+  // LDS-DMA path, ahead of the ring's first steps: the compiler cannot count
+  // the DMA loads, so its wait for any load it issues after them would drain
+  // the ring. Rows past the end load row 0's queries and are zeroed.
   const int row = v * 16 + i;
+  lds_dma4(a.ctx_len + r, &s_misc[wave][0][0]);
+  lds_dma4(map_addr(smap, ks, mask_slot(0), a.ctx_len + r), &s_misc[wave][1][0]);
+  lds_dma4(map_addr(smap, ks, mask_slot(1), a.ctx_len + r), &s_misc[wave][2][0]);
   {
     const int qr = row < a.rows ? row : 0;
     const int tq = qr / a.G;
     const int qh = h * a.G + (qr - tq * a.G);
-    const uint16_t* qrow = a.q + (((long long)r * a.T + tq) * a.Hq + qh) * kHeadDim;
-    lds_dma4(a.ctx_len + r, &s_misc[v][0][0]);
-    lds_dma4(map_addr(smap, ks, mask_slot(0), a.ctx_len + r), &s_misc[v][1][0]);
-    lds_dma4(map_addr(smap, ks, mask_slot(kChunkU), a.ctx_len + r), &s_misc[v][2][0]);
+    const uint32_t qoff = (uint32_t)(((tq * a.Hq + qh) * kHeadDim + g * 8) * 2);
+    const uint16_t* qbase = a.q + (long long)r * a.T * a.Hq * kHeadDim;
+    // a tile's 4 k-steps are loaded by its wave of the first team
+    if (team == 0) {
 #pragma unroll
-    for (int st = 0; st < 4; ++st) lds_dma16(qrow + st * 32 + g * 8, &s_q[v][st][0]);
+      for (int st = 0; st < 4; ++st) lds_dma16(qbase + st * 32, qoff, &s_q[v][st][0]);
+    }
   }
-  static_for<kRowsStages - 1>([&](auto S) __attribute__((always_inline)) { issue(decltype(S)::value, S); });
-  wait_vmcnt<kPer * (kRowsStages - 1)>();  // all but the ring's units are in
+  // units of the first kLook steps go out before the slot map is known
+  auto unit = [&](int t) __attribute__((always_inline)) { return u_begin + t < u_end ? u_begin + t : -1; };
+#pragma unroll
+  for (int st = 0; st < kLook; ++st) issue(unit(st * kTeams + team), st);
+  wait_vmcnt<kPer * kLook>();  // all but the ring's steps are in
+  __syncthreads();             // the other team's queries too
 
   // Q^T operand of row tile v
-  bf16x8 qb[1][4];
+  bf16x8 qb[4];
 #pragma unroll
-  for (int st = 0; st < 4; ++st) qb[0][st] = as_bf16x8(row < a.rows ? s_q[v][st][lane] : u32x4{0, 0, 0, 0});
-  const Ctx c = ctx_blocks(__builtin_amdgcn_readfirstlane(s_misc[v][0][lane]), BS, a.NBmax);
+  for (int st = 0; st < 4; ++st) qb[st] = as_bf16x8(row < a.rows ? s_q[v][st][lane] : u32x4{0, 0, 0, 0});
+  const Ctx c = ctx_blocks(__builtin_amdgcn_readfirstlane(s_misc[wave][0][lane]), BS, a.NBmax);
   const int local_len = c.local_len;
-
-  float m_run[1] = {-INFINITY}, l_run[1] = {0.f};
-  f32x4 acc[1][8];
-#pragma unroll
-  for (int dt = 0; dt < 8; ++dt) acc[0][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-  uint64_t vmask = map_mask(ks, mask_slot(0), s_misc[v][1][lane]);
-  const bf16x8(&q1)[4] = qb[0];
-
-  // The previous unit's scores, V operands and mask, finished one step late:
-  // before the first unit they stand for an empty unit (no token attended).
-  f32x4 sc_prev[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-  u32x4 v_prev[8];
-#pragma unroll
-  for (int dt = 0; dt < 8; ++dt) v_prev[dt] = u32x4{0, 0, 0, 0};
-  int keep_prev = 0;
-  bool partial_prev = true;
-
-  // unit t sits in stage t % kRowsStages
-  auto step = [&](int t, auto S) __attribute__((always_inline)) {
-    constexpr int k = decltype(S)::value;
-    // this wave's loads of unit t are done (those of the kRowsStages - 2 later units may
-    // still fly); the barrier publishes every wave's loads of unit t and tells that the
-    // stage of unit t - 1 is no longer read
-    wait_vmcnt<kPer * (kRowsStages - 2)>();
-    __syncthreads();
-    if (t > 0 && (t & (kChunkU - 1)) == 0) {
-      // mask chunk t / kChunkU came in a chunk ago; the next one goes out now
-      // (one more load ahead of the next unit's only makes later waits stricter)
-      const int ch = t / kChunkU;
-      vmask = map_mask(ks, mask_slot(t), s_misc[v][1 + (ch & 1)][lane]);
-      lds_dma4(map_addr(smap, ks, mask_slot(t + kChunkU), a.ctx_len + r), &s_misc[v][1 + ((ch + 1) & 1)][0]);
-    }
-    issue(t + kRowsStages - 1, std::integral_constant<int, (k + kRowsStages - 1) % kRowsStages>{});
-    const UnitLds& buf = stage_buf(S);
-    UnitRegs cur;
-#pragma unroll
-    for (int tau = 0; tau < 2; ++tau)
-#pragma unroll
-      for (int st = 0; st < 4; ++st) cur.k[tau][st] = buf[tau * 4 + st][lane];
-#pragma unroll
-    for (int dt = 0; dt < 8; ++dt) cur.v[dt] = buf[8 + dt][lane];
-    f32x4 sc[2];
-    unit_scores(cur, q1, sc);
-    // the previous unit's softmax and PV products run beside this unit's score products
-    unit_softmax_pv(sc_prev, v_prev, keep_prev, partial_prev, m_run[0], l_run[0], acc[0], a.scale_log2);
+  int chunk = 0;
+  uint64_t vmask = map_mask(ks, mask_slot(0), s_misc[wave][1][lane]);
+  // attended tokens of the slots of the split's unit t (in the current mask chunk), n0 | n1 << 8
+  auto counts = [&](int t) __attribute__((always_inline)) {
     int n0, n1;
-    const int bit = BS == 16 ? 2 * (t & (kChunkU - 1)) : (t & (kChunkU - 1));
-    unit_counts<BS>(unit(t), ks, local_len, vmask, bit, n0, n1);
-    keep_prev = lane_keep<BS>(n0, n1, g);
-    partial_prev = __builtin_amdgcn_ballot_w64(keep_prev < 8) != 0;
-    sc_prev[0] = sc[0];
-    sc_prev[1] = sc[1];
-#pragma unroll
-    for (int dt = 0; dt < 8; ++dt) v_prev[dt] = cur.v[dt];
+    unit_counts<BS>(unit(t), ks, local_len, vmask, BS == 16 ? 2 * (t & (kChunk - 1)) : (t & (kChunk - 1)), n0, n1);
+    return n0 | n1 << 8;
   };
-  int t = 0;
-  for (; t + kRowsStages <= nt; t += kRowsStages)
-    static_for<kRowsStages>([&](auto S) __attribute__((always_inline)) { step(t + decltype(S)::value, S); });
-  static_for<kRowsStages - 1>([&](auto S) __attribute__((always_inline)) {
-    if (t + decltype(S)::value < nt) step(t + decltype(S)::value, S);
-  });
-  unit_softmax_pv(sc_prev, v_prev, keep_prev, partial_prev, m_run[0], l_run[0], acc[0], a.scale_log2);
-  wait_vmcnt<0>();  // the placeholder loads past the last unit land before the workgroup ends
-  float L = l_run[0] + __shfl_xor(l_run[0], 16);
+
+  float m_run = -INFINITY, l_run = 0.f;
+  f32x4 acc[8];
+#pragma unroll
+  for (int dt = 0; dt < 8; ++dt) acc[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  const int nt = u_end > u_begin ? u_end - u_begin : 0;
+  const int nsteps = (nt + kTeams - 1) / kTeams;
+  int cnt[kLook];
+#pragma unroll
+  for (int st = 0; st < kLook; ++st) cnt[st] = counts(st * kTeams + team);
+  int stage = 0;
+  for (int s = 0; s < nsteps; ++s) {
+    // this wave's loads of step s are done (those of the later step may still fly); the
+    // barrier publishes every wave's loads of step s and tells that the stage of step
+    // s - 1 is no longer read
+    wait_vmcnt<kPer * (kLook - 1)>();
+    __syncthreads();
+    const int tn = (s + kLook) * kTeams + team;
+    const int ch = tn / kChunk;
+    if (ch != chunk) {
+      // the map entries of chunk ch came in while the chunk before was attended; the next ones go out now
+      chunk = ch;
+      vmask = map_mask(ks, mask_slot(ch), s_misc[wave][1 + (ch & 1)][lane]);
+      lds_dma4(map_addr(smap, ks, mask_slot(ch + 1), a.ctx_len + r), &s_misc[wave][1 + ((ch + 1) & 1)][0]);
+    }
+    const int nstage = stage == 0 ? kRowsStages - 1 : stage - 1;  // (s + kLook) % kRowsStages
+    issue(unit(tn), nstage);
+    const u32x4(&buf)[16][64] = s_ring[stage][team];
+    f32x4 sc[2];
+    // all of the unit's operands are read at once (left alone, the compiler reads
+    // a K chunk, waits for it, and reads the next); the two token tiles' chains alternate
+    u32x4 kr[8], vr[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) kr[j] = buf[j][lane];
+    __builtin_amdgcn_sched_barrier(0);
+    sc[0] = sc[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int st = 0; st < 4; ++st)
+#pragma unroll
+      for (int tau = 0; tau < 2; ++tau)
+        sc[tau] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(kr[tau * 4 + st]), qb[st], sc[tau], 0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) vr[j] = buf[8 + j][lane];
+    __builtin_amdgcn_sched_barrier(0);
+    const int keep = lane_keep<BS>(cnt[0] & 0xFF, cnt[0] >> 8, g);
+    const bool partial = __builtin_amdgcn_ballot_w64(keep < 8) != 0;
+    unit_softmax_pv(sc, keep, partial, m_run, l_run, acc, a.scale_log2, [&](int dt) { return vr[dt]; });
+#pragma unroll
+    for (int st = 0; st + 1 < kLook; ++st) cnt[st] = cnt[st + 1];
+    cnt[kLook - 1] = counts(tn);
+    stage = stage == kRowsStages - 1 ? 0 : stage + 1;
+  }
+  wait_vmcnt<0>();  // the placeholder loads past the last unit land before the ring is reused
+
+  float L = l_run + __shfl_xor(l_run, 16);
   L += __shfl_xor(L, 32);
-  const float M = m_run[0];
+  float M = m_run;
+  // ---- merge the two teams: each takes one half of the dimensions of the row
+  // tiles, d-tiles 4 * team .. +4, and gets the other team's part of them through LDS
+  constexpr int kHalf = kHeadDim / 2 + 4;
+  float(*s_o)[16][kHalf] = reinterpret_cast<float(*)[16][kHalf]>(&s_ring[0][0][0][0]);  // [wave]
+  float(*s_ml)[2][16] = reinterpret_cast<float(*)[2][16]>(&s_q[0][0][0]);               // [wave]
+  static_assert(sizeof(float) * 32 * kWaves <= sizeof(s_q), "maxima and sums fit the query area");
+  static_assert(sizeof(float) * 16 * kHalf * kWaves <= sizeof(s_ring), "the states fit the ring");
+  __syncthreads();  // the ring and the queries are no longer read
+  f32x4 mine[4];
+#pragma unroll
+  for (int dt = 0; dt < 4; ++dt) {
+    mine[dt] = team == 0 ? acc[dt] : acc[dt + 4];
+    *reinterpret_cast<f32x4*>(&s_o[wave][i][dt * 16 + 4 * g]) = team == 0 ? acc[dt + 4] : acc[dt];
+  }
+  if (g == 0) {
+    s_ml[wave][0][i] = M;
+    s_ml[wave][1][i] = L;
+  }
+  __syncthreads();
   if (row >= a.rows) return;
+  const int other = wave < NT ? wave + NT : wave - NT;
+  const float mo = s_ml[other][0][i], lo = s_ml[other][1][i];
+  const float mm = fmaxf(M, mo);
+  const float f = M == -INFINITY ? 0.f : fast_exp2(M - mm);
+  const float fo = mo == -INFINITY ? 0.f : fast_exp2(mo - mm);
+  L = L * f + lo * fo;
+  M = mm;
+#pragma unroll
+  for (int dt = 0; dt < 4; ++dt)
+    mine[dt] = mine[dt] * f + *reinterpret_cast<const f32x4*>(&s_o[other][i][dt * 16 + 4 * g]) * fo;
   if (a.nsplit == 1) {
 #pragma unroll
-    for (int dt = 0; dt < 8; ++dt) write_output(a, r, h, row, dt * 4 + g, acc[0][dt], M, L);
+    for (int dt = 0; dt < 4; ++dt) write_output(a, r, h, row, (team * 4 + dt) * 4 + g, mine[dt], M, L);
     return;
   }
   const long long pr = ((long long)rh * a.nsplit + split) * a.rows + row;
 #pragma unroll
-  for (int dt = 0; dt < 8; ++dt) *reinterpret_cast<f32x4*>(a.part_o + pr * kHeadDim + dt * 16 + 4 * g) = acc[0][dt];
-  if (g == 0) *reinterpret_cast<float2*>(a.part_ml + pr * 2) = make_float2(M, L);
+  for (int dt = 0; dt < 4; ++dt)
+    *reinterpret_cast<f32x4*>(a.part_o + pr * kHeadDim + (team * 4 + dt) * 16 + 4 * g) = mine[dt];
+  if (team == 0 && g == 0) *reinterpret_cast<float2*>(a.part_ml + pr * 2) = make_float2(M, L);
 }
 
 // Merge of the NS splits: a workgroup takes kMergeRows rows of one (request,
@@ -899,7 +890,7 @@ hipError_t launch_t(const AttnArgs& a, hipStream_t s, const LaunchTiming& t) {
   const bool merge = a.nsplit > 1;
   // timed as one span: from the split kernel's start to the merge kernel's end
   if constexpr (NT >= 3)
-    launch_kernel(attn_split_rows_kernel<NT, BS>, dim3(xcd_grid(nrh, a.nsplit)), dim3(NT * 64), s,
+    launch_kernel(attn_split_rows_kernel<NT, BS>, dim3(xcd_grid(nrh, a.nsplit)), dim3(NT * kTeams * 64), s,
                   LaunchTiming{t.start, merge ? nullptr : t.stop}, a);
   else
     launch_kernel(attn_split_kernel<NT, BS>, dim3(xcd_grid(nrh, a.nsplit)), dim3(kW * 64), s,
@@ -953,7 +944,7 @@ AttnPlan attn_plan(int R, int Hq, int Hkv, int T, int B, int k_slots) {
   if (p.nsplit > 1 && nrh * p.nsplit > kTargetWorkgroups) want = kTargetWorkgroups / nrh;
   // With more than 16 rows to merge, a few units more per split and fewer splits
   // (1 request x 8 KV heads, 20 rows: 13 splits of 5 units 10.8 us, 11 of 6 10.4
-  // us; 8 rows: 8.3 us either way).
+  // us; 40 rows 12.4 and 11.9 us; 8 rows: 8.3 us either way).
   split(want, p.rows <= 16 ? kW : 6);
   // partials exist only with several splits (one split writes the outputs itself)
   p.part_o_floats = p.nsplit > 1 ? (size_t)nrh * p.nsplit * p.rows * kHeadDim : 0;
