@@ -42,17 +42,26 @@ __device__ __forceinline__ void score_q_store(ScoreQOperands<NRT>& s_q, int e, u
   s_q[e >> 8][(e >> 6) & 3][1][e & 63] = m;
 }
 
-// Summary rows of block tile*16 + n for lane (g, n): 16 bytes at 64*step + 16*g
-// of the kmax row and of the kmin row (zero past the candidates).
-__device__ __forceinline__ void score_tile_load(const uint16_t* kmx, const uint16_t* kmn, int tile, int n_cand,
-                                                int g, int n, u32x4 (&vmax)[4], u32x4 (&vmin)[4]) {
-  const int blk = tile * 16 + n;
-  const bool live = blk < n_cand;
+// Summary rows of the TPW tiles from tile0 (tile0 * 16 < n_cand): lane (g, n)
+// gets 16 bytes at 64*step + 16*g of the kmax and of the kmin row of block
+// tile*16 + n. Blocks past the candidates re-read the last one (a cache hit;
+// their scores are never written). Every address is a wave-uniform base plus a
+// 32-bit lane offset and a constant, so the loads hold no 64-bit addresses in
+// vector registers.
+template <int TPW>
+__device__ __forceinline__ void score_tiles_load(const uint16_t* kmx, const uint16_t* kmn, int tile0, int n_cand,
+                                                 int g, int n, u32x4 (&vmax)[TPW][4], u32x4 (&vmin)[TPW][4]) {
+  const char* bx = reinterpret_cast<const char*>(kmx + (long long)tile0 * 16 * kHeadDim);
+  const char* bn = reinterpret_cast<const char*>(kmn + (long long)tile0 * 16 * kHeadDim);
+  const int last = n_cand - 1 - tile0 * 16;
 #pragma unroll
-  for (int st = 0; st < 4; ++st) {
-    const long long off = (long long)blk * kHeadDim + st * 32 + g * 8;
-    vmax[st] = live ? ldg16(kmx + off) : u32x4{0, 0, 0, 0};
-    vmin[st] = live ? ldg16(kmn + off) : u32x4{0, 0, 0, 0};
+  for (int t = 0; t < TPW; ++t) {
+    const uint32_t o = (uint32_t)(min(t * 16 + n, last) * kHeadDim + g * 8) * 2;
+#pragma unroll
+    for (int st = 0; st < 4; ++st) {
+      vmax[t][st] = ldg16(bx + o + st * 64);
+      vmin[t][st] = ldg16(bn + o + st * 64);
+    }
   }
 }
 

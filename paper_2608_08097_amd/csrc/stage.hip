@@ -129,11 +129,6 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Lanes below this one whose bit is set in `mask`.
-__device__ __forceinline__ int lanes_below(uint64_t mask) {
-  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-}
-
 // Shared-memory arrays of a plan pass (kMaxK items, kMaxPairs pairs).
 struct PlanLds {
   int *sel, *hit, *map, *stamp, *keep, *selpage;
@@ -998,7 +993,8 @@ __global__ __launch_bounds__(kSelThreads) void topk_plan_kernel(TopkArgs t, Stag
   const int rh = blockIdx.x;
   const int r = rh / t.Hkv;
   const Ctx c = ctx_blocks(t.ctx_len[r], t.B, t.NBmax);
-  select_row<kSelThreads, KPT>(t.scores + (long long)rh * t.NBmax, c.n_cand, t.k, t.sel + (long long)rh * t.k,
+  const float* s = t.scores + (long long)rh * t.NBmax;
+  select_row<kSelThreads, KPT>([&](int i) { return select_key(s[i]); }, c.n_cand, t.k, t.sel + (long long)rh * t.k,
                                t.sel_count + rh, sh, s_lsel);
   __syncthreads();
   const int m = c.n_cand < t.k ? (c.n_cand > 0 ? c.n_cand : 0) : t.k;
@@ -1010,49 +1006,67 @@ __global__ __launch_bounds__(kSelThreads) void topk_plan_kernel(TopkArgs t, Stag
 // every block of the head; §4.2.2: top-K prediction; §4.2.3: delta selection).
 // The workgroup scores its row's candidate tiles with the scorer's MFMA pieces
 // (score_core.h, so the scores are bit-identical to the scoring kernel's),
-// writes the row of scores, and selects from it after a workgroup barrier, so
-// no other workgroup is waited for. The query operands sit in the selection's
-// key staging area until the selection starts. Each wave scores kScoreSelTiles
-// tiles at a time, all their loads issued before the first MFMA. Small
-// workgroups let several rows share a CU, so that one row's selection overlaps
-// another's loads. Worth trying where the rows are many and short, so that one
-// workgroup per row fills the chip; with few long rows the two kernels spread
-// a row over many workgroups.
-constexpr int kScoreSelThreads = 256;
-constexpr int kScoreSelTiles = 4;
+// writes the row of scores, leaves its selection keys in LDS and selects from
+// them after a workgroup barrier, so no other workgroup is waited for and no
+// score is read back. Each wave scores kScoreSelTiles tiles at a time; the first
+// ones' loads go out before the query operands are in, each later round's before
+// the reductions of the one before. Worth trying where the rows are many and
+// short, so that one workgroup per row fills the chip; with few long rows the
+// two kernels spread a row over many workgroups.
+//
+// With as many rows as CUs or a few more, all rows load and then all select, so
+// the selection's latency is not hidden by other rows' loads, and more waves per
+// row shorten both phases. Measured on MI355X (16 scoring rows, contexts of 5K to
+// 17K tokens), 48 requests x 8 KV heads (142 MB): 256 threads x 4 tiles with the
+// keys read back from memory 43.3 us, keys in LDS and early loads 38.9, 512 x 2
+// 37.8, 512 x 4 39.0, 1024 x 2 38.8; 90 requests (265 MB) 72.9, 63.1, 60.2, 62.9
+// and 62.3 us.
+constexpr int kScoreSelThreads = 512;
+constexpr int kScoreSelTiles = 2;
 
 template <int NRT, int KPT, bool PLAN>
 __global__ __launch_bounds__(kScoreSelThreads) void score_select_kernel(ScoreArgs sa, TopkArgs t, StageArgs a) {
   constexpr int NTHR = kScoreSelThreads;
   constexpr int TPW = kScoreSelTiles;
-  __shared__ __align__(16) SelectShared<NTHR, KPT> sh;
+  constexpr int kStep = (NTHR / 64) * TPW;  // tiles per round of the workgroup
+  __shared__ SelectShared<NTHR, KPT> sh;
+  __shared__ __align__(16) ScoreQOperands<NRT> s_q;
+  __shared__ uint32_t s_keys[NTHR * KPT];  // the row's keys
   __shared__ int s_lsel[PLAN ? kMaxK : 1];
   __shared__ int s_slot[PLAN ? kMaxK + kMaxPairs : 1], s_page[PLAN ? kMaxK + kMaxPairs : 1];
   __shared__ int s_epair[PLAN ? kMaxK + kMaxPairs : 1];
   __shared__ int s_prh[PLAN ? kMaxPairs : 1];
   __shared__ int s_wave[NTHR / 64 + 1];
-  static_assert(sizeof(ScoreQOperands<NRT>) <= sizeof(sh.keys), "query operands must fit the key staging area");
   const int rh = blockIdx.x;
   const int r = rh / sa.Hkv;
   const int h = rh - r * sa.Hkv;
-  const int wave = threadIdx.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int g = lane >> 4;
   const int n = lane & 15;
   const Ctx c = ctx_blocks(sa.ctx_len[r], sa.B, sa.NBmax);
-  ScoreQOperands<NRT>& s_q = *reinterpret_cast<ScoreQOperands<NRT>*>(sh.keys);
-  for (int e = threadIdx.x; e < NRT * 256; e += NTHR) score_q_store<NRT>(s_q, e, score_q_raw(sa, r, h, e));
-
   const long long sum_base = (long long)rh * sa.NBmax * kHeadDim;
   const uint16_t* kmx = sa.kmax + sum_base;
   const uint16_t* kmn = sa.kmin + sum_base;
   float* srow = sa.scores + (long long)rh * sa.NBmax;
   const int ntile_c = (c.n_cand + 15) >> 4;
-  __syncthreads();  // query operands are in
-  for (int tile0 = wave * TPW; tile0 < ntile_c; tile0 += (NTHR / 64) * TPW) {
-    u32x4 vmax[TPW][4], vmin[TPW][4];
+  constexpr int kQ = (NRT * 256 + NTHR - 1) / NTHR;
+  u32x4 qraw[kQ];
 #pragma unroll
-    for (int u = 0; u < TPW; ++u) score_tile_load(kmx, kmn, tile0 + u, c.n_cand, g, n, vmax[u], vmin[u]);
+  for (int j = 0; j < kQ; ++j) {
+    const int e = threadIdx.x + j * NTHR;
+    qraw[j] = score_q_raw(sa, r, h, e < NRT * 256 ? e : 0);
+  }
+  // the first tiles' loads go out before the query operands are waited for
+  u32x4 vmax[TPW][4], vmin[TPW][4];
+  if (wave * TPW < ntile_c) score_tiles_load<TPW>(kmx, kmn, wave * TPW, c.n_cand, g, n, vmax, vmin);
+#pragma unroll
+  for (int j = 0; j < kQ; ++j) {
+    const int e = threadIdx.x + j * NTHR;
+    if (e < NRT * 256) score_q_store<NRT>(s_q, e, qraw[j]);
+  }
+  __syncthreads();  // query operands are in
+  for (int tile0 = wave * TPW; tile0 < ntile_c; tile0 += kStep) {
     float best[TPW];
 #pragma unroll
     for (int u = 0; u < TPW; ++u) best[u] = -INFINITY;
@@ -1063,17 +1077,22 @@ __global__ __launch_bounds__(kScoreSelThreads) void score_select_kernel(ScoreArg
 #pragma unroll
       for (int u = 0; u < TPW; ++u) best[u] = score_tile_fold(ap, an, vmax[u], vmin[u], best[u]);
     }
+    // the next round's loads run beside this round's reductions
+    if (tile0 + kStep < ntile_c) score_tiles_load<TPW>(kmx, kmn, tile0 + kStep, c.n_cand, g, n, vmax, vmin);
 #pragma unroll
     for (int u = 0; u < TPW; ++u) {
       const float b = score_lane_reduce(best[u]);
       const int blk = (tile0 + u) * 16 + n;
-      if (g == 0 && blk < c.n_cand) srow[blk] = b;
+      if (g == 0 && blk < c.n_cand) {
+        srow[blk] = b;
+        s_keys[blk] = select_key(b);
+      }
     }
   }
   for (int b = c.n_cand + threadIdx.x; b < sa.NBmax; b += NTHR) srow[b] = -INFINITY;
-  __syncthreads();  // the score row is complete, and the query operands are no longer read
-  select_row<NTHR, KPT>(srow, c.n_cand, t.k, t.sel + (long long)rh * t.k, t.sel_count + rh, sh,
-                        PLAN ? s_lsel : nullptr);
+  __syncthreads();  // every key is in
+  select_row<NTHR, KPT>([&](int i) { return s_keys[i]; }, c.n_cand, t.k, t.sel + (long long)rh * t.k,
+                        t.sel_count + rh, sh, PLAN ? s_lsel : nullptr);
   if (PLAN) {
     __syncthreads();
     const int m = c.n_cand < t.k ? (c.n_cand > 0 ? c.n_cand : 0) : t.k;
@@ -1095,14 +1114,12 @@ hipError_t launch_score_select_t(const ScoreArgs& sa, const TopkArgs& t, const S
 template <int NRT>
 hipError_t launch_score_select_nrt(const ScoreArgs& sa, const TopkArgs& t, const StageArgs* plan, hipStream_t s,
                                    const LaunchTiming& lt) {
-  // keys per thread; the staged keys also hold the query operands (8 KiB per row tile)
   const int per = (sa.NBmax + kScoreSelThreads - 1) / kScoreSelThreads;
-  if constexpr (NRT == 1) {
-    if (per <= 8) return launch_score_select_t<NRT, 8>(sa, t, plan, s, lt);
-  }
-  if (per <= 16) return launch_score_select_t<NRT, 16>(sa, t, plan, s, lt);
-  if (per <= 32) return launch_score_select_t<NRT, 32>(sa, t, plan, s, lt);
-  return launch_score_select_t<NRT, 64>(sa, t, plan, s, lt);
+  constexpr int kMost = kScoreSelectMaxBlocks / kScoreSelThreads;  // keys per thread of the longest row
+  if (per <= kMost / 8) return launch_score_select_t<NRT, kMost / 8>(sa, t, plan, s, lt);
+  if (per <= kMost / 4) return launch_score_select_t<NRT, kMost / 4>(sa, t, plan, s, lt);
+  if (per <= kMost / 2) return launch_score_select_t<NRT, kMost / 2>(sa, t, plan, s, lt);
+  return launch_score_select_t<NRT, kMost>(sa, t, plan, s, lt);
 }
 
 }  // namespace
