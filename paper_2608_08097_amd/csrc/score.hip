@@ -21,6 +21,11 @@
 // 134 MB) 30.1 us against 38.5 us (4 waves per SIMD instead of 2); 16 rows
 // (8 x 131,072 tokens, 268 MB) 48.6 us against 49.9 us (fewer query reads;
 // 3, 5, 6 and 8 summary tiles per wave: 48.6, 50.8, 51.7 and 56.6 us).
+// Summary addresses are a wave-uniform base and a 32-bit lane offset
+// (score_tiles_load): per-lane 64-bit addresses and zero-filled lanes past the
+// candidates took registers that cost a wave per SIMD. Scores and selection
+// before and after: the 64-row case 35.0 -> 32.1 us, the 16-row case 56.7 ->
+// 55.6, 32 requests of 16K-32K tokens (16 rows, 204 MB) 49.7 -> 46.1 us.
 #include "oasis_internal.h"
 #include "score_core.h"
 
@@ -36,7 +41,7 @@ namespace {
 // rather than once per wave.
 template <int NRT, int TPW>
 __global__ __launch_bounds__(256) void score_kernel(ScoreArgs a) {
-  const int wave = threadIdx.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int g = lane >> 4;
   const int n = lane & 15;
@@ -51,6 +56,7 @@ __global__ __launch_bounds__(256) void score_kernel(ScoreArgs a) {
   // blocks) would leave their XCDs idle; rotating the group by the row spreads
   // every group over all XCDs (ragged 16K-32K-token rows: 48.0 -> 47.0 us).
   const int group = (int)((blockIdx.x + blockIdx.y) % gridDim.x);
+  float* srow = a.scores + (long long)rh * a.NBmax;
   const int tile0 = (group * 4 + wave) * TPW;
   __shared__ ScoreQOperands<NRT> s_q;
 
@@ -61,21 +67,11 @@ __global__ __launch_bounds__(256) void score_kernel(ScoreArgs a) {
   const long long sum_base = (long long)rh * a.NBmax * kHeadDim;
   const uint16_t* kmx = a.kmax + sum_base;
   const uint16_t* kmn = a.kmin + sum_base;
-  // (the loads are written out here rather than through score_tile_load: with
-  // both helpers the compiler keeps far more registers live, 284 VGPRs instead
-  // of 116 at four row tiles, one wave per SIMD instead of four)
   u32x4 vmax[TPW][4], vmin[TPW][4];
-#pragma unroll
-  for (int t = 0; t < TPW; ++t) {
-    const int blk = (tile0 + t) * 16 + n;
-    const bool live = blk < c.n_cand;
-#pragma unroll
-    for (int st = 0; st < 4; ++st) {
-      const long long off = (long long)blk * kHeadDim + st * 32 + g * 8;
-      vmax[t][st] = live ? ldg16(kmx + off) : u32x4{0, 0, 0, 0};
-      vmin[t][st] = live ? ldg16(kmn + off) : u32x4{0, 0, 0, 0};
-    }
-  }
+  // a wave past the candidates reads one row instead (returning before the
+  // loads made every wave wait for the context length first: 1 us at 8,191 blocks)
+  const bool alive = tile0 * 16 < c.n_cand;
+  score_tiles_load<TPW>(kmx, kmn, alive ? tile0 : 0, alive ? c.n_cand : 1, g, n, vmax, vmin);
 #pragma unroll
   for (int j = 0; j < NRT; ++j) score_q_store<NRT>(s_q, threadIdx.x + j * 256, qraw[j]);
   __syncthreads();  // every wave reaches it: waves past the last tile return only below
@@ -84,7 +80,7 @@ __global__ __launch_bounds__(256) void score_kernel(ScoreArgs a) {
   float best[TPW];
 #pragma unroll
   for (int t = 0; t < TPW; ++t) best[t] = -INFINITY;
-  if (tile0 * 16 < c.n_cand) {
+  if (alive) {
 #pragma unroll
     for (int v = 0; v < NRT; ++v) {
       bf16x8 ap[4], an[4];
@@ -93,7 +89,6 @@ __global__ __launch_bounds__(256) void score_kernel(ScoreArgs a) {
       for (int t = 0; t < TPW; ++t) best[t] = score_tile_fold(ap, an, vmax[t], vmin[t], best[t]);
     }
   }
-  float* srow = a.scores + (long long)rh * a.NBmax;
 #pragma unroll
   for (int t = 0; t < TPW; ++t) {
     const int tile = tile0 + t;
