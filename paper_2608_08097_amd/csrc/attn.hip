@@ -492,7 +492,7 @@ __global__ __launch_bounds__(kW * 64) void attn_split_kernel(AttnArgs a) {
 // V cross HBM once: its 16 chunks (8 of K, 8 of V, 16 bytes a lane, in the MFMA
 // operand layout of load_unit) are loaded straight into LDS, and one wave per
 // row tile reads all 16 back as conflict-free 16-byte LDS reads. A workgroup
-// has two such teams of waves, on alternate units: with one team (3 to 5 waves)
+// has two such teams of waves, on alternate units (kTeams = 1: launch_t): with one (3 to 5 waves)
 // a unit's chain of LDS reads, score products, softmax and PV products paces
 // the loads, since a SIMD then has one wave, or none, to issue from. A step
 // holds one unit per team; a ring of kRowsStages steps keeps kRowsStages - 1 in
@@ -509,7 +509,6 @@ __global__ __launch_bounds__(kW * 64) void attn_split_kernel(AttnArgs a) {
 // used: reading a K chunk, waiting and reading the next took 47 us at the first.
 // Short splits pay for the second team's part of the merge: 16 pairs in 15
 // splits of 9 units 17.4 us, one team 16.3.
-constexpr int kTeams = 2;
 constexpr int kRowsStages = 3;
 // 16 bytes a lane from global memory (base + offset, base wave-uniform) straight
 // into LDS (global_load_lds_dwordx4): lane L's bytes land at lds_row + 16 L,
@@ -607,7 +606,7 @@ __device__ __forceinline__ void unit_softmax_pv(const f32x4 (&sc)[2], int keep, 
     acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(v[dt]), pb, acc[dt], 0, 0, 0);
 }
 
-template <int NT, int BS>
+template <int NT, int kTeams, int BS>
 __global__ __launch_bounds__(NT * kTeams * 64) void attn_split_rows_kernel(AttnArgs a) {
   constexpr int kWaves = NT * kTeams;
   constexpr int kPer = (16 + NT - 1) / NT;  // chunk loads per wave and step
@@ -765,46 +764,61 @@ __global__ __launch_bounds__(NT * kTeams * 64) void attn_split_rows_kernel(AttnA
   float L = l_run + __shfl_xor(l_run, 16);
   L += __shfl_xor(L, 32);
   float M = m_run;
-  // ---- merge the two teams: each takes one half of the dimensions of the row
-  // tiles, d-tiles 4 * team .. +4, and gets the other team's part of them through LDS
-  constexpr int kHalf = kHeadDim / 2 + 4;
-  float(*s_o)[16][kHalf] = reinterpret_cast<float(*)[16][kHalf]>(&s_ring[0][0][0][0]);  // [wave]
-  float(*s_ml)[2][16] = reinterpret_cast<float(*)[2][16]>(&s_q[0][0][0]);               // [wave]
-  static_assert(sizeof(float) * 32 * kWaves <= sizeof(s_q), "maxima and sums fit the query area");
-  static_assert(sizeof(float) * 16 * kHalf * kWaves <= sizeof(s_ring), "the states fit the ring");
-  __syncthreads();  // the ring and the queries are no longer read
-  f32x4 mine[4];
+  static_assert(kTeams == 1 || kTeams == 2, "the merge below");
+  if constexpr (kTeams == 1) {
+    if (row >= a.rows) return;
+    if (a.nsplit == 1) {
 #pragma unroll
-  for (int dt = 0; dt < 4; ++dt) {
-    mine[dt] = team == 0 ? acc[dt] : acc[dt + 4];
-    *reinterpret_cast<f32x4*>(&s_o[wave][i][dt * 16 + 4 * g]) = team == 0 ? acc[dt + 4] : acc[dt];
+      for (int dt = 0; dt < 8; ++dt) write_output(a, r, h, row, dt * 4 + g, acc[dt], M, L);
+      return;
+    }
+    const long long pr = ((long long)rh * a.nsplit + split) * a.rows + row;
+#pragma unroll
+    for (int dt = 0; dt < 8; ++dt)
+      *reinterpret_cast<f32x4*>(a.part_o + pr * kHeadDim + dt * 16 + 4 * g) = acc[dt];
+    if (g == 0) *reinterpret_cast<float2*>(a.part_ml + pr * 2) = make_float2(M, L);
+  } else {
+    // ---- merge the two teams: each takes one half of the dimensions of the row
+    // tiles, d-tiles 4 * team .. +4, and gets the other team's part of them through LDS
+    constexpr int kHalf = kHeadDim / 2 + 4;
+    float(*s_o)[16][kHalf] = reinterpret_cast<float(*)[16][kHalf]>(&s_ring[0][0][0][0]);  // [wave]
+    float(*s_ml)[2][16] = reinterpret_cast<float(*)[2][16]>(&s_q[0][0][0]);               // [wave]
+    static_assert(sizeof(float) * 32 * kWaves <= sizeof(s_q), "maxima and sums fit the query area");
+    static_assert(sizeof(float) * 16 * kHalf * kWaves <= sizeof(s_ring), "the states fit the ring");
+    __syncthreads();  // the ring and the queries are no longer read
+    f32x4 mine[4];
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt) {
+      mine[dt] = team == 0 ? acc[dt] : acc[dt + 4];
+      *reinterpret_cast<f32x4*>(&s_o[wave][i][dt * 16 + 4 * g]) = team == 0 ? acc[dt + 4] : acc[dt];
+    }
+    if (g == 0) {
+      s_ml[wave][0][i] = M;
+      s_ml[wave][1][i] = L;
+    }
+    __syncthreads();
+    if (row >= a.rows) return;
+    const int other = wave < NT ? wave + NT : wave - NT;
+    const float mo = s_ml[other][0][i], lo = s_ml[other][1][i];
+    const float mm = fmaxf(M, mo);
+    const float f = M == -INFINITY ? 0.f : fast_exp2(M - mm);
+    const float fo = mo == -INFINITY ? 0.f : fast_exp2(mo - mm);
+    L = L * f + lo * fo;
+    M = mm;
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+      mine[dt] = mine[dt] * f + *reinterpret_cast<const f32x4*>(&s_o[other][i][dt * 16 + 4 * g]) * fo;
+    if (a.nsplit == 1) {
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt) write_output(a, r, h, row, (team * 4 + dt) * 4 + g, mine[dt], M, L);
+      return;
+    }
+    const long long pr = ((long long)rh * a.nsplit + split) * a.rows + row;
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+      *reinterpret_cast<f32x4*>(a.part_o + pr * kHeadDim + (team * 4 + dt) * 16 + 4 * g) = mine[dt];
+    if (team == 0 && g == 0) *reinterpret_cast<float2*>(a.part_ml + pr * 2) = make_float2(M, L);
   }
-  if (g == 0) {
-    s_ml[wave][0][i] = M;
-    s_ml[wave][1][i] = L;
-  }
-  __syncthreads();
-  if (row >= a.rows) return;
-  const int other = wave < NT ? wave + NT : wave - NT;
-  const float mo = s_ml[other][0][i], lo = s_ml[other][1][i];
-  const float mm = fmaxf(M, mo);
-  const float f = M == -INFINITY ? 0.f : fast_exp2(M - mm);
-  const float fo = mo == -INFINITY ? 0.f : fast_exp2(mo - mm);
-  L = L * f + lo * fo;
-  M = mm;
-#pragma unroll
-  for (int dt = 0; dt < 4; ++dt)
-    mine[dt] = mine[dt] * f + *reinterpret_cast<const f32x4*>(&s_o[other][i][dt * 16 + 4 * g]) * fo;
-  if (a.nsplit == 1) {
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt) write_output(a, r, h, row, (team * 4 + dt) * 4 + g, mine[dt], M, L);
-    return;
-  }
-  const long long pr = ((long long)rh * a.nsplit + split) * a.rows + row;
-#pragma unroll
-  for (int dt = 0; dt < 4; ++dt)
-    *reinterpret_cast<f32x4*>(a.part_o + pr * kHeadDim + (team * 4 + dt) * 16 + 4 * g) = mine[dt];
-  if (team == 0 && g == 0) *reinterpret_cast<float2*>(a.part_ml + pr * 2) = make_float2(M, L);
 }
 
 // Merge of the NS splits: a workgroup takes kMergeRows rows of one (request,
@@ -889,12 +903,23 @@ hipError_t launch_t(const AttnArgs& a, hipStream_t s, const LaunchTiming& t) {
   const long long nrh = (long long)a.R * a.Hkv;
   const bool merge = a.nsplit > 1;
   // timed as one span: from the split kernel's start to the merge kernel's end
-  if constexpr (NT >= 3)
-    launch_kernel(attn_split_rows_kernel<NT, BS>, dim3(xcd_grid(nrh, a.nsplit)), dim3(NT * kTeams * 64), s,
-                  LaunchTiming{t.start, merge ? nullptr : t.stop}, a);
-  else
-    launch_kernel(attn_split_kernel<NT, BS>, dim3(xcd_grid(nrh, a.nsplit)), dim3(kW * 64), s,
-                  LaunchTiming{t.start, merge ? nullptr : t.stop}, a);
+  const LaunchTiming ts{t.start, merge ? nullptr : t.stop};
+  if constexpr (NT >= 3) {
+    // With more pairs than CUs there are no splits, and at most two pairs per CU
+    // fit it together with one team each (two teams' ring fills the LDS), instead
+    // of in two rounds. Measured with two teams against one (8 KV heads, 40 rows,
+    // budget 1,024): 33 requests 46.3 and 37.3 us, 60 requests 52.9 and 49.2; past
+    // two pairs per CU level (70 requests 72.9 and 71.4). Five row tiles' single
+    // teams hold a CU less well together: 33 requests 52.3 and 66.5 us.
+    constexpr bool kShare = NT <= 4;
+    if (kShare && nrh > kTargetWorkgroups && nrh <= 2 * kTargetWorkgroups)
+      launch_kernel(attn_split_rows_kernel<NT, kShare ? 1 : 2, BS>, dim3(xcd_grid(nrh, a.nsplit)),
+                    dim3(NT * (kShare ? 1 : 2) * 64), s, ts, a);
+    else
+      launch_kernel(attn_split_rows_kernel<NT, 2, BS>, dim3(xcd_grid(nrh, a.nsplit)), dim3(NT * 2 * 64), s, ts, a);
+  } else {
+    launch_kernel(attn_split_kernel<NT, BS>, dim3(xcd_grid(nrh, a.nsplit)), dim3(kW * 64), s, ts, a);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !merge) return e;
   launch_merge(a, s, LaunchTiming{nullptr, t.stop});
@@ -942,10 +967,16 @@ AttnPlan attn_plan(int R, int Hq, int Hkv, int T, int B, int k_slots) {
   // one: 3 requests 17.3 against 12.8 us, 5 requests 18.1 and 13.0, 17 requests
   // 43.0 and 33.6, 22 requests (two splits against one, no merge) 46.3 and 35.5.
   if (p.nsplit > 1 && nrh * p.nsplit > kTargetWorkgroups) want = kTargetWorkgroups / nrh;
-  // With more than 16 rows to merge, a few units more per split and fewer splits
-  // (1 request x 8 KV heads, 20 rows: 13 splits of 5 units 10.8 us, 11 of 6 10.4
-  // us; 40 rows 12.4 and 11.9 us; 8 rows: 8.3 us either way).
-  split(want, p.rows <= 16 ? kW : 6);
+  split(want, p.rows <= 32 ? kW : 6);
+  // Fewer splits where no wave's chain gets longer: 65 units in 13 splits of 5
+  // leave one wave of four with two units, and so do 9 splits of 8 (1 request x 8
+  // KV heads, 20 rows, per call: 10.8 and 10.5 us; 2 requests 12.1 and 11.4 us).
+  // One row tile has little to merge (8.3 against 8.5 us), and the many-row
+  // kernel's two teams take at least three units each (72 rows: 14.1 -> 13.6 us).
+  if (p.rows > 16 && p.rows <= 32 && p.nsplit > 1) {
+    const int depth = (p.units_per_split + kW - 1) / kW;
+    split((p.n_units + depth * kW - 1) / (depth * kW), kW);
+  }
   // partials exist only with several splits (one split writes the outputs itself)
   p.part_o_floats = p.nsplit > 1 ? (size_t)nrh * p.nsplit * p.rows * kHeadDim : 0;
   return p;

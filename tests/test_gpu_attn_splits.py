@@ -28,6 +28,9 @@ CASES = [
     (11, 17, 64, 8, 9, 16, 25, "tail"),      # the same with five row tiles, an odd unit count
     (12, 5, 32, 8, 8, 32, 33, "random"),     # 40 pairs x 32 rows: six splits, not seven
     (13, 33, 16, 8, 5, 16, 16, "tail"),      # 264 pairs: more than CUs
+    (14, 43, 24, 6, 9, 16, 12, "random"),    # 258 pairs x 36 rows: many-row kernel, one team per pair
+    (15, 65, 64, 8, 7, 32, 5, "random"),     # 520 pairs x 56 rows: more than two per CU
+    (16, 1, 16, 1, 3, 16, 130, "random"),    # 48 rows, 66 units: many short splits
 ]
 
 
