@@ -6,6 +6,11 @@ them (device or pinned host), have the right dtype and are contiguous, then
 pass raw pointers and the current HIP stream. Every step of the path runs in
 the library's kernels; there is no fallback. If the library is not built, the
 first call raises.
+
+The calls a decode step makes many times first go to ``_fastcall`` (built
+beside the library), which makes the same checks and the call natively and
+returns None for arguments it does not accept as they are; those, and every
+error, take the Python code below it.
 """
 from __future__ import annotations
 
@@ -61,6 +66,7 @@ def dims(num_reqs, num_q_heads, num_kv_heads, head_dim, block_size, max_blocks) 
 
 
 _lib = None
+_fast = None  # the _fastcall module, bound to the loaded library
 ABI_VERSION = 7  # OASIS_ABI_VERSION of include/oasis.h
 
 _P = ctypes.c_void_p
@@ -138,8 +144,24 @@ def lib() -> ctypes.CDLL:
         L.oasis_pipeline_profile_end.restype = _I32
         L.oasis_pipeline_profile_end.argtypes = [_P, ctypes.POINTER(ctypes.c_float), ctypes.POINTER(ctypes.c_float),
                                                    ctypes.POINTER(_I32)]
+        _bind_fast(L)
         _lib = L
     return _lib
+
+
+def _bind_fast(L: ctypes.CDLL) -> None:
+    """Point the native marshalling at the entry points of the loaded library."""
+    global _fast
+    from . import _fastcall
+    _fastcall.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+        L.oasis_sparse_decode_attn, L.oasis_score_blocks, L.oasis_select_topk, L.oasis_score_select,
+        L.oasis_stage_blocks)))
+    _fast = _fastcall
+
+
+def _handle(stream):
+    """The stream as the native marshalling takes it: a handle, or None for the current stream."""
+    return None if stream is None else _stream(stream)
 
 
 def _check(fn: str, status: int) -> None:
@@ -249,6 +271,11 @@ def oasis_copy_blocks(d: OasisDims, src_k, src_v, src_block_table, dst_k, dst_v,
 
 def oasis_score_blocks(d: OasisDims, q, num_q_tokens: int, first_draft: int, num_draft: int,
                        kmax, kmin, ctx_len, scores, stream=None) -> None:
+    if _fast is not None and type(d) is OasisDims:
+        st = _fast.score_blocks(ctypes.addressof(d), q, num_q_tokens, first_draft, num_draft, kmax, kmin, ctx_len,
+                                scores, _handle(stream))
+        if st is not None:
+            return _check("oasis_score_blocks", st)
     R, H, NB, D = d.num_reqs, d.num_kv_heads, d.max_blocks, d.head_dim
     _need(q, R * num_q_tokens * d.num_q_heads * D, "q")
     _need(kmax, R * H * NB * D, "kmax")
@@ -262,6 +289,10 @@ def oasis_score_blocks(d: OasisDims, q, num_q_tokens: int, first_draft: int, num
 
 
 def oasis_select_topk(d: OasisDims, scores, ctx_len, k: int, sel, sel_count, stream=None) -> None:
+    if _fast is not None and type(d) is OasisDims:
+        st = _fast.select_topk(ctypes.addressof(d), scores, ctx_len, k, sel, sel_count, _handle(stream))
+        if st is not None:
+            return _check("oasis_select_topk", st)
     R, H = d.num_reqs, d.num_kv_heads
     _need(scores, R * H * d.max_blocks, "scores")
     _need(ctx_len, R, "ctx_len")
@@ -275,6 +306,11 @@ def oasis_select_topk(d: OasisDims, scores, ctx_len, k: int, sel, sel_count, str
 def oasis_score_select(d: OasisDims, q, num_q_tokens: int, first_draft: int, num_draft: int, kmax, kmin, ctx_len,
                        k: int, scores, sel, sel_count, stream=None) -> None:
     """Scores and top-K in one kernel (the same results as oasis_score_blocks + oasis_select_topk)."""
+    if _fast is not None and type(d) is OasisDims:
+        st = _fast.score_select(ctypes.addressof(d), q, num_q_tokens, first_draft, num_draft, kmax, kmin, ctx_len, k,
+                                scores, sel, sel_count, _handle(stream))
+        if st is not None:
+            return _check("oasis_score_select", st)
     R, H, NB, D = d.num_reqs, d.num_kv_heads, d.max_blocks, d.head_dim
     _need(q, R * num_q_tokens * d.num_q_heads * D, "q")
     _need(kmax, R * H * NB * D, "kmax")
@@ -295,6 +331,12 @@ def oasis_stage_blocks(d: OasisDims, host_k, host_v, host_block_table, ctx_len, 
                        moved, stream=None) -> None:
     if host_k.shape != host_v.shape:
         raise ValueError("host_k and host_v differ in shape")
+    if _fast is not None and type(d) is OasisDims:
+        st = _fast.stage_blocks(ctypes.addressof(d), host_k, host_v, host_k.shape[0], host_block_table, ctx_len, sel,
+                                sel_count, scores, k, slot_map, slot_stamp, step, fetch_cap, copy_local, pool_k,
+                                pool_v, moved, _handle(stream))
+        if st is not None:
+            return _check("oasis_stage_blocks", st)
     R, H, B, D = d.num_reqs, d.num_kv_heads, d.block_size, d.head_dim
     _need(host_k, host_k.shape[0] * H * B * D, "host_k")
     _need(host_block_table, R * d.max_blocks, "host_block_table")
@@ -333,6 +375,11 @@ def oasis_attn_workspace_bytes(d: OasisDims, num_q_tokens: int, k_slots: int) ->
 
 def oasis_sparse_decode_attn(d: OasisDims, q, num_q_tokens: int, pool_k, pool_v, slot_map, k_slots: int,
                              ctx_len, scale: float | None, out, lse, workspace, stream=None) -> None:
+    if _fast is not None and type(d) is OasisDims:
+        st = _fast.sparse_decode_attn(ctypes.addressof(d), q, num_q_tokens, pool_k, pool_v, slot_map, k_slots, ctx_len,
+                                      scale, out, lse, workspace, _handle(stream))
+        if st is not None:
+            return _check("oasis_sparse_decode_attn", st)
     if scale is None:
         scale = 1.0 / math.sqrt(d.head_dim)
     R, H, B, D = d.num_reqs, d.num_kv_heads, d.block_size, d.head_dim

@@ -1,4 +1,5 @@
-"""Build liboasis.so (all HIP kernels + the C ABI) for gfx950 with hipcc, in-tree."""
+"""Build liboasis.so (all HIP kernels + the C ABI) for gfx950 with hipcc, and the binding's native
+marshalling (_fastcall.so) with the host compiler, in-tree."""
 from __future__ import annotations
 
 import glob
@@ -43,12 +44,26 @@ def flags() -> list[str]:
 FILE_FLAGS = {"attn.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
+FASTCALL_PATH = os.path.join(PKG_DIR, "_fastcall.so")
+
+
+def fastcall_cmd(out: str) -> list[str]:
+    """The host compiler's command for the extension module (PyTorch's headers and libraries)."""
+    import sysconfig
+    from torch.utils import cpp_extension as ext
+    inc = [*ext.include_paths("cpu"), sysconfig.get_paths()["include"], "/opt/rocm/include"]
+    return [os.environ.get("CXX") or "g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-Wall",
+            "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", "-I", os.path.join(ROOT, "include"),
+            *(f"-isystem{p}" for p in inc), os.path.join(PKG_DIR, "csrc", "fastcall.cpp"), "-o", out,
+            *(f"-L{p}" for p in ext.library_paths("cpu")), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+
+
 def _run(cmd: list[str]) -> str:
     res = subprocess.run(cmd, capture_output=True, text=True)
     noise = "is not a recognized feature for this target"
     err = "\n".join(l for l in res.stderr.splitlines() if noise not in l)
     if res.returncode != 0:
-        raise RuntimeError(f"hipcc failed ({res.returncode}): {' '.join(cmd)}\n{err}")
+        raise RuntimeError(f"{os.path.basename(cmd[0])} failed ({res.returncode}): {' '.join(cmd)}\n{err}")
     return err
 
 
@@ -65,6 +80,8 @@ def build(verbose: bool = False) -> str:
         jobs = len(os.sched_getaffinity(0))
     except AttributeError:  # pragma: no cover
         jobs = os.cpu_count() or 1
+    fast_tmp = FASTCALL_PATH + ".tmp"
+    cmds.append(fastcall_cmd(fast_tmp))
     with ThreadPoolExecutor(max_workers=max(1, min(16, jobs))) as ex:
         errs = list(ex.map(_run, cmds))
     tmp = LIB_PATH + ".tmp"
@@ -77,6 +94,7 @@ def build(verbose: bool = False) -> str:
         if err:
             print(err, file=sys.stderr)
     os.replace(tmp, LIB_PATH)
+    os.replace(fast_tmp, FASTCALL_PATH)
     return LIB_PATH
 
 

@@ -1,0 +1,127 @@
+"""The native marshalling accepts exactly the plain calls: what it does not accept goes to the Python binding,
+whose errors are unchanged, and what it accepts gives the binding's results on the binding's stream."""
+import ctypes
+
+import pytest
+import torch
+
+import paper_2608_08097_amd as P
+from paper_2608_08097_amd import _lib as L
+
+R, H, G, T, NB, B, K = 2, 2, 4, 3, 40, 16, 8
+
+
+def _tensors(device):
+    bf, i32 = torch.bfloat16, torch.int32
+    g = torch.Generator().manual_seed(3)
+
+    def rand(*s):
+        return torch.randn(s, generator=g).to(bf).to(device)
+
+    a, b = rand(R, H, NB, 128), rand(R, H, NB, 128)
+    pages = 64
+    return dict(d=P.dims(R, H * G, H, 128, B, NB), q=rand(R, T, H * G, 128), kmax=torch.maximum(a, b),
+                kmin=torch.minimum(a, b), ctx=torch.tensor([NB * B, 300], dtype=i32, device=device),
+                scores=torch.zeros(R, H, NB, device=device), sel=torch.zeros(R, H, K, dtype=i32, device=device),
+                cnt=torch.zeros(R, H, dtype=i32, device=device),
+                table=torch.arange(R * NB, dtype=i32, device=device).remainder(pages).view(R, NB).contiguous(),
+                host_k=rand(pages, H, B, 128), host_v=rand(pages, H, B, 128),
+                smap=torch.full((R, H, K), -1, dtype=i32, device=device),
+                stamp=torch.zeros(R, H, K, dtype=i32, device=device), pool_k=torch.zeros(R, K + 1, H, B, 128, dtype=bf, device=device),
+                pool_v=torch.zeros(R, K + 1, H, 128, B, dtype=bf, device=device),
+                moved=torch.zeros(R, H, dtype=i32, device=device), out=torch.zeros(R, T, H * G, 128, dtype=bf, device=device),
+                lse=torch.zeros(R, T, H * G, device=device),
+                ws=torch.zeros(1 << 20, dtype=torch.uint8, device=device))
+
+
+def _step(t, stream=None):
+    d = t["d"]
+    P.oasis_score_blocks(d, t["q"], T, 1, T - 1, t["kmax"], t["kmin"], t["ctx"], t["scores"], stream)
+    P.oasis_select_topk(d, t["scores"], t["ctx"], K, t["sel"], t["cnt"], stream)
+    P.oasis_stage_blocks(d, t["host_k"], t["host_v"], t["table"], t["ctx"], t["sel"], t["cnt"], t["scores"], K,
+                         t["smap"], t["stamp"], 1, K, True, t["pool_k"], t["pool_v"], t["moved"], stream)
+    P.oasis_sparse_decode_attn(d, t["q"], T, t["pool_k"], t["pool_v"], t["smap"], K, t["ctx"], None, t["out"],
+                               t["lse"], t["ws"], stream)
+    P.oasis_score_select(d, t["q"], T, 1, T - 1, t["kmax"], t["kmin"], t["ctx"], K, t["scores"], t["sel"], t["cnt"],
+                         stream)
+
+
+class _Sub(torch.Tensor):
+    pass
+
+
+def _args(t):
+    return [ctypes.addressof(t["d"]), t["scores"], t["ctx"], K, t["sel"], t["cnt"], None]
+
+
+def test_unusual_forms_are_not_accepted():
+    """On the CPU: no form below may reach the library (a host tensor, other types and counts, a subclass)."""
+    L.lib()
+    t = _tensors("cpu")
+    call = L._fast.select_topk
+    assert call(*_args(t)) is None  # host tensors
+    for i, x in ((1, None), (1, 5), (3, 8.0), (3, True), (3, 1 << 40), (4, t["sel"].as_subclass(_Sub)), (6, "0")):
+        a = _args(t)
+        a[i] = x
+        assert call(*a) is None, (i, x)
+    assert call(*_args(t)[:-1]) is None
+    with pytest.raises(ValueError, match="scores must be a device tensor"):
+        P.oasis_select_topk(t["d"], t["scores"], t["ctx"], K, t["sel"], t["cnt"], 0)
+
+
+@pytest.mark.gpu
+def test_checks_and_results_match_the_python_binding():
+    L.lib()
+    t = _tensors("cuda")
+    torch.cuda.synchronize()
+    for i, x in ((1, t["scores"].double()), (1, t["scores"].transpose(0, 1)), (2, t["ctx"][:1]), (4, t["sel"].long()),
+                 (5, t["cnt"].cpu()), (4, t["sel"].as_subclass(_Sub))):
+        a = _args(t)
+        a[i] = x
+        assert L._fast.select_topk(*a) is None, i
+    with pytest.raises(TypeError, match="scores: dtype"):
+        P.oasis_select_topk(t["d"], t["scores"].double(), t["ctx"], K, t["sel"], t["cnt"])
+    with pytest.raises(ValueError, match="sel: 7 elements"):
+        P.oasis_select_topk(t["d"], t["scores"], t["ctx"], K, t["sel"].view(-1)[:7], t["cnt"])
+    with pytest.raises(P.OasisError, match="k = 0"):  # accepted and refused by the library
+        P.oasis_select_topk(t["d"], t["scores"], t["ctx"], 0, t["sel"][:0], t["cnt"])
+    outs = []
+    side = torch.cuda.Stream()
+    for fast, stream in ((True, None), (False, None), (True, side), (True, "current")):
+        t = _tensors("cuda")
+        torch.cuda.synchronize()
+        keep = L._fast
+        L._fast = keep if fast else None
+        try:
+            if stream == "current":
+                with torch.cuda.stream(side):
+                    _step(t)
+            else:
+                _step(t, stream)
+        finally:
+            L._fast = keep
+        torch.cuda.synchronize()
+        outs.append([t[n].clone() for n in ("scores", "sel", "cnt", "smap", "stamp", "pool_k", "pool_v", "moved",
+                                            "out", "lse")])
+    for other in outs[1:]:
+        assert all(torch.equal(x, y) for x, y in zip(outs[0], other))
+
+
+@pytest.mark.gpu
+def test_capture_takes_the_current_stream():
+    """A captured step replays on its own stream and gives the eager results, replay after replay."""
+    t, ref = _tensors("cuda"), _tensors("cuda")
+    _step(ref)
+    _step(t)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        _step(t)
+    for _ in range(3):
+        for n in ("scores", "sel", "cnt", "out", "lse"):
+            t[n].zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        for n in ("scores", "sel", "cnt", "out", "lse", "smap", "pool_k"):
+            assert torch.equal(t[n], ref[n]), n
