@@ -106,8 +106,11 @@ __device__ __forceinline__ UnitOffsets unit_offsets(long long slot_elems, int g,
 // u < 0 is a placeholder unit: the loads are issued anyway (every lane on the
 // first bytes of the local slot, one cache line) and count nothing. Issuing the
 // same number of loads on every path keeps the compiler's wait counts exact,
-// so waiting for the current unit never drains the prefetched one.
-template <int BS>
+// so waiting for the current unit never drains the prefetched one. With STREAM
+// (kStreamBytes) V is read past the caches; K is not, since two of its loads
+// share each line (22 requests x 8 heads, 187 MB: plain 36.9 us, V 32.2, K 37.7,
+// both 37.5).
+template <int BS, bool STREAM>
 __device__ __forceinline__ void load_unit(UnitRegs& ur, int u, int ks, const uint16_t* pk, const uint16_t* pv,
                                           long long slot_elems, const UnitOffsets& o) {
   const bool real = u >= 0;
@@ -122,7 +125,7 @@ __device__ __forceinline__ void load_unit(UnitRegs& ur, int u, int ks, const uin
 #pragma unroll
     for (int st = 0; st < 4; ++st) ur.k[tau][st] = ldg16(kb + ok + (tau * 4 * kHeadDim + st * 32) * 2);
 #pragma unroll
-  for (int dt = 0; dt < 8; ++dt) ur.v[dt] = ldg16(vb + ov + dt * 16 * BS * 2);
+  for (int dt = 0; dt < 8; ++dt) ur.v[dt] = ldg16_once<STREAM>(vb + ov + dt * 16 * BS * 2);
 }
 
 // Attended tokens of the two slots of unit u (u < 0: none): a slot below k_slots
@@ -269,7 +272,7 @@ __device__ __forceinline__ uint64_t map_mask(int ks, int slot, int entry) {
 // against 104 us when every slot is read. Every unit's addresses are a
 // wave-uniform base and a 32-bit lane offset (UnitOffsets); 64-bit vector
 // addresses took 17.9 against 16.9 us at 8 x 131,072 tokens (68 MB).
-template <int NT, int BS>
+template <int NT, int BS, bool STREAM>
 __global__ __launch_bounds__(kW * 64) void attn_split_kernel(AttnArgs a) {
   static_assert(NT <= 2, "three or more row tiles take attn_split_rows_kernel");
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
@@ -301,7 +304,7 @@ __global__ __launch_bounds__(kW * 64) void attn_split_kernel(AttnArgs a) {
   // by waiting for a scalar or query load; the queries, the slot map and the
   // context length follow.
   UnitRegs ua, ub;
-  load_unit<BS>(ua, unit(0), ks, pk, pv, slot_elems, uo);
+  load_unit<BS, STREAM>(ua, unit(0), ks, pk, pv, slot_elems, uo);
 
   // Q^T operand: lane (g, i) holds row v*16 + i of tile v, dims st*32 + 8g .. +8.
   bf16x8 qb[NT][4];
@@ -324,7 +327,7 @@ __global__ __launch_bounds__(kW * 64) void attn_split_kernel(AttnArgs a) {
   // next unit's loads are out, so that the wait for it comes after them
   int ctx_raw = __hip_atomic_load(a.ctx_len + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   __builtin_amdgcn_sched_barrier(0);
-  load_unit<BS>(ub, unit(1), ks, pk, pv, slot_elems, uo);
+  load_unit<BS, STREAM>(ub, unit(1), ks, pk, pv, slot_elems, uo);
   __builtin_amdgcn_sched_barrier(0);  // both units' loads are issued before the first wait
 
   float m_run[NT], l_run[NT];  // row reference maximum (log2 units) and this lane's partial sum
@@ -392,11 +395,11 @@ __global__ __launch_bounds__(kW * 64) void attn_split_kernel(AttnArgs a) {
     run(ua, na0, na1);
     if (tb >= nt) break;
     ta = next_unit(tb);
-    load_unit<BS>(ua, unit(ta), ks, pk, pv, slot_elems, uo);
+    load_unit<BS, STREAM>(ua, unit(ta), ks, pk, pv, slot_elems, uo);
     counts(ta, na0, na1);
     run(ub, nb0, nb1);
     tb = next_unit(ta);
-    load_unit<BS>(ub, unit(tb), ks, pk, pv, slot_elems, uo);
+    load_unit<BS, STREAM>(ub, unit(tb), ks, pk, pv, slot_elems, uo);
     counts(tb, nb0, nb1);
     if (ta >= nt) break;
   }
@@ -519,19 +522,31 @@ constexpr int kRowsStages = 3;
 // explicit vmcnt counts of the kernel instead. The "memory" clobber keeps LDS
 // reads and writes in program order around it, and M0 (the LDS base operand
 // of the load) is restored after it.
+template <bool STREAM = false>
 __device__ __forceinline__ void lds_dma16(const void* base, uint32_t offset, void* lds_row) {
   const uint32_t lds =
       __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds_row);
   uint32_t saved;
-  asm volatile(
-      "s_mov_b32 %0, m0\n\t"
-      "s_mov_b32 m0, %3\n\t"
-      "s_nop 0\n\t"
-      "global_load_lds_dwordx4 %1, %2\n\t"
-      "s_mov_b32 m0, %0"
-      : "=&s"(saved)
-      : "v"(offset), "s"(base), "s"(lds)
-      : "memory");
+  if constexpr (STREAM)
+    asm volatile(
+        "s_mov_b32 %0, m0\n\t"
+        "s_mov_b32 m0, %3\n\t"
+        "s_nop 0\n\t"
+        "global_load_lds_dwordx4 %1, %2 nt\n\t"
+        "s_mov_b32 m0, %0"
+        : "=&s"(saved)
+        : "v"(offset), "s"(base), "s"(lds)
+        : "memory");
+  else
+    asm volatile(
+        "s_mov_b32 %0, m0\n\t"
+        "s_mov_b32 m0, %3\n\t"
+        "s_nop 0\n\t"
+        "global_load_lds_dwordx4 %1, %2\n\t"
+        "s_mov_b32 m0, %0"
+        : "=&s"(saved)
+        : "v"(offset), "s"(base), "s"(lds)
+        : "memory");
 }
 
 // 4 bytes a lane, as lds_dma16 (lane L's bytes land at lds_row + 4 L).
@@ -606,7 +621,7 @@ __device__ __forceinline__ void unit_softmax_pv(const f32x4 (&sc)[2], int keep, 
     acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(v[dt]), pb, acc[dt], 0, 0, 0);
 }
 
-template <int NT, int kTeams, int BS>
+template <int NT, int kTeams, int BS, bool STREAM>
 __global__ __launch_bounds__(NT * kTeams * 64) void attn_split_rows_kernel(AttnArgs a) {
   constexpr int kWaves = NT * kTeams;
   constexpr int kPer = (16 + NT - 1) / NT;  // chunk loads per wave and step
@@ -654,7 +669,7 @@ __global__ __launch_bounds__(NT * kTeams * 64) void attn_split_rows_kernel(AttnA
       const uint32_t off = is_k ? (two ? uo.k1 : uo.k0) : (two ? uo.v1 : uo.v0);
       const uint16_t* base = (is_k ? pk : pv) + slot +
                              (is_k ? (j >> 2) * 4 * kHeadDim + (j & 3) * 32 : j < 16 ? (j - 8) * 16 * BS : 0);
-      lds_dma16(base, real && j < 16 ? off : 0u, j < 16 ? &s_ring[st][team][j][0] : &s_junk[0]);
+      lds_dma16<STREAM>(base, real && j < 16 ? off : 0u, j < 16 ? &s_ring[st][team][j][0] : &s_junk[0]);
     }
   };
   // validity mask chunks: units ch * kChunk .. of the split (lane l: map entry of
@@ -904,6 +919,10 @@ hipError_t launch_t(const AttnArgs& a, hipStream_t s, const LaunchTiming& t) {
   const bool merge = a.nsplit > 1;
   // timed as one span: from the split kernel's start to the merge kernel's end
   const LaunchTiming ts{t.start, merge ? nullptr : t.stop};
+  // Bytes at most: no context has more than NBmax blocks. (Counting every slot at
+  // contexts a quarter of the pool took 21.9 -> 23.1 us.)
+  const long long blocks = a.k_slots + 1ll < a.NBmax ? a.k_slots + 1ll : a.NBmax;
+  const bool stream = nrh * blocks * BS * (2 * kHeadDim * 2) >= kStreamBytes;
   if constexpr (NT >= 3) {
     // With more pairs than CUs there are no splits, and at most two pairs per CU
     // fit it together with one team each (two teams' ring fills the LDS), instead
@@ -912,13 +931,21 @@ hipError_t launch_t(const AttnArgs& a, hipStream_t s, const LaunchTiming& t) {
     // two pairs per CU level (70 requests 72.9 and 71.4). Five row tiles' single
     // teams hold a CU less well together: 33 requests 52.3 and 66.5 us.
     constexpr bool kShare = NT <= 4;
+    // Reading past the caches (kStreamBytes) pays here at B = 32 where the CUs are
+    // full, so that bandwidth bounds the call: 128 pairs in two splits (72 rows, 274
+    // MB) 61.7 -> 54.1 us, 256 pairs 106 -> 94.5; at 176 of 256 workgroups 74.6 and
+    // 79.8 us, and at B = 16, where half a wave reads each slot, 44.4 and 47.7.
+    const bool fill = BS == 32 && stream && 8 * nrh * a.nsplit >= 7 * kTargetWorkgroups;
+    const dim3 grid(xcd_grid(nrh, a.nsplit));
     if (kShare && nrh > kTargetWorkgroups && nrh <= 2 * kTargetWorkgroups)
-      launch_kernel(attn_split_rows_kernel<NT, kShare ? 1 : 2, BS>, dim3(xcd_grid(nrh, a.nsplit)),
-                    dim3(NT * (kShare ? 1 : 2) * 64), s, ts, a);
+      launch_kernel(attn_split_rows_kernel<NT, kShare ? 1 : 2, BS, false>, grid, dim3(NT * (kShare ? 1 : 2) * 64), s, ts,
+                    a);
     else
-      launch_kernel(attn_split_rows_kernel<NT, 2, BS>, dim3(xcd_grid(nrh, a.nsplit)), dim3(NT * 2 * 64), s, ts, a);
+      launch_kernel(fill ? attn_split_rows_kernel<NT, 2, BS, BS == 32> : attn_split_rows_kernel<NT, 2, BS, false>, grid,
+                    dim3(NT * 2 * 64), s, ts, a);
   } else {
-    launch_kernel(attn_split_kernel<NT, BS>, dim3(xcd_grid(nrh, a.nsplit)), dim3(kW * 64), s, ts, a);
+    launch_kernel(stream ? attn_split_kernel<NT, BS, true> : attn_split_kernel<NT, BS, false>,
+                  dim3(xcd_grid(nrh, a.nsplit)), dim3(kW * 64), s, ts, a);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !merge) return e;

@@ -28,6 +28,23 @@ __device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {
 
 __device__ __forceinline__ u32x4 ldg16(const void* p) { return *reinterpret_cast<const u32x4*>(p); }
 
+// Calls that read at least this much mark their loads non-temporal where whole
+// cache lines are read by one instruction: the data cannot wait in the 256 MB
+// Infinity Cache for its next use beside anything else, and keeping it there
+// only costs. Measured on MI355X over rotating buffers, plain against
+// non-temporal: attention of 136 pairs (144 MB) 31.0 and 25.2 us, of 256 (272 MB)
+// 48.3 and 44.5, of 720 (761 MB) 123 and 114; 96 pairs (102 MB) 23.7 and 22.5,
+// 80 pairs (85 MB) level, 64 pairs (68 MB, found in the cache again) 16.9 and
+// 17.1; summaries of 1.2 GB 238 and 211, of 75 MB 12.9 and 14.6. Where two
+// instructions share a line (the MFMA scorer's and the attention's K operands,
+// 64 bytes a row) it is slower: scores of 204 MB 46.4 and 51.8 us.
+constexpr long long kStreamBytes = 96ll << 20;
+template <bool STREAM>
+__device__ __forceinline__ u32x4 ldg16_once(const void* p) {
+  if constexpr (STREAM) return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+  else return ldg16(p);
+}
+
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
 // Number of logical blocks, candidate blocks and local-block tokens of a context.

@@ -15,7 +15,8 @@
 // head_dim, and the maximum over the draft rows is kept in the lane. Lanes past the
 // candidates re-read the last candidate block (a cache hit) and write -inf; a
 // wave past them all only writes (64 requests of 5K-17K tokens in 1,088-block
-// rows, with the selection: 46.2 -> 44.9 us).
+// rows, with the selection: 46.2 -> 44.9 us). Large calls read past the caches
+// (kStreamBytes): the same 44.1 -> 39.1 us, 8 x 131,072 tokens 58.3 -> 52.5.
 #include "oasis_internal.h"
 
 namespace oasis {
@@ -49,7 +50,7 @@ __device__ __forceinline__ float row16_sum(float s) {
   return s;
 }
 
-template <int ROWS>
+template <int ROWS, bool STREAM>
 __global__ __launch_bounds__(256) void score_valu_kernel(ScoreArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
@@ -76,8 +77,8 @@ __global__ __launch_bounds__(256) void score_valu_kernel(ScoreArgs a) {
 #pragma unroll
   for (int gi = 0; gi < kGroups; ++gi) {
     const int blk = min(blk0 + 4 * gi + j, last);
-    vmax[gi] = ldg16(a.kmax + base + (long long)blk * kHeadDim);
-    vmin[gi] = ldg16(a.kmin + base + (long long)blk * kHeadDim);
+    vmax[gi] = ldg16_once<STREAM>(a.kmax + base + (long long)blk * kHeadDim);
+    vmin[gi] = ldg16_once<STREAM>(a.kmin + base + (long long)blk * kHeadDim);
   }
 
   // [q+ | q-] of this lane's slice for every row; rows past the last real row
@@ -118,7 +119,8 @@ template <int ROWS>
 hipError_t launch_rows(const ScoreArgs& a, hipStream_t s, const LaunchTiming& t) {
   constexpr int kPerWorkgroup = 4 * 4 * kGroups;  // 4 waves x 32 blocks
   const dim3 grid((unsigned)((a.NBmax + kPerWorkgroup - 1) / kPerWorkgroup), (unsigned)(a.R * a.Hkv));
-  launch_kernel(score_valu_kernel<ROWS>, grid, dim3(256), s, t, a);
+  const bool stream = (long long)a.R * a.Hkv * a.NBmax * (2 * kHeadDim * 2) >= kStreamBytes;
+  launch_kernel(stream ? score_valu_kernel<ROWS, true> : score_valu_kernel<ROWS, false>, grid, dim3(256), s, t, a);
   return hipGetLastError();
 }
 

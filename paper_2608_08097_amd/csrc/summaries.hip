@@ -8,14 +8,17 @@
 // first is used (B is a template parameter, so the token loop unrolls);
 // neighbouring threads cover neighbouring dimensions, so a wave reads whole
 // 256-byte key rows. The result is exact: min/max of bf16 values is a bf16
-// value.
+// value. Bound by HBM: a large build reads and writes past the caches
+// (from 2 * kStreamBytes of keys), 4 prompts of 24K-32K tokens (262 MB) 55.7 ->
+// 47.7 us, 8 x 65,536 tokens (1.2 GB) 238 -> 211 us, loads alone 222 us; at 91
+// MB it would take 18.7 us against 17.4.
 #include "oasis_internal.h"
 
 namespace oasis {
 
 namespace {
 
-template <int BS>
+template <int BS, bool STREAM>
 __global__ __launch_bounds__(256) void summaries_kernel(SummaryArgs a) {
   const int r = blockIdx.y;
   const long long item = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -40,7 +43,7 @@ __global__ __launch_bounds__(256) void summaries_kernel(SummaryArgs a) {
   }
   u32x4 rows[BS];
 #pragma unroll
-  for (int p = 0; p < BS; ++p) rows[p] = ldg16(src + (long long)p * kHeadDim);
+  for (int p = 0; p < BS; ++p) rows[p] = ldg16_once<STREAM>(src + (long long)p * kHeadDim);
 #pragma unroll
   for (int p = 0; p < BS; ++p) {
     const u32x4 v = rows[p];
@@ -62,8 +65,13 @@ __global__ __launch_bounds__(256) void summaries_kernel(SummaryArgs a) {
     omn[w] = (__float_as_uint(mn[2 * w]) >> 16) | (__float_as_uint(mn[2 * w + 1]) & 0xFFFF0000u);
   }
   const long long o = (((long long)r * a.Hkv + h) * a.NBmax + b) * kHeadDim + d0;
-  *reinterpret_cast<u32x4*>(a.kmax + o) = omx;
-  *reinterpret_cast<u32x4*>(a.kmin + o) = omn;
+  if constexpr (STREAM) {
+    __builtin_nontemporal_store(omx, reinterpret_cast<u32x4*>(a.kmax + o));
+    __builtin_nontemporal_store(omn, reinterpret_cast<u32x4*>(a.kmin + o));
+  } else {
+    *reinterpret_cast<u32x4*>(a.kmax + o) = omx;
+    *reinterpret_cast<u32x4*>(a.kmin + o) = omn;
+  }
 }
 
 }  // namespace
@@ -72,10 +80,12 @@ hipError_t launch_summaries(const SummaryArgs& a, hipStream_t s) {
   const long long blocks = a.prev_ctx_len ? (a.max_new < a.NBmax ? a.max_new : a.NBmax) : a.NBmax;
   const long long items = blocks * a.Hkv * (kHeadDim / 8);
   const dim3 grid((unsigned)((items + 255) / 256), (unsigned)a.R);
+  // (later than other calls: what a build writes is read next, by the scorer)
+  const bool stream = a.R * items * a.B * 16 >= 2 * kStreamBytes;
   if (a.B == 16)
-    hipLaunchKernelGGL(summaries_kernel<16>, grid, dim3(256), 0, s, a);
+    launch_kernel(stream ? summaries_kernel<16, true> : summaries_kernel<16, false>, grid, dim3(256), s, {}, a);
   else if (a.B == 32)
-    hipLaunchKernelGGL(summaries_kernel<32>, grid, dim3(256), 0, s, a);
+    launch_kernel(stream ? summaries_kernel<32, true> : summaries_kernel<32, false>, grid, dim3(256), s, {}, a);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();

@@ -72,3 +72,58 @@ def test_attn_splits(seed, R, Hq, Hkv, T, B, ks, kind):
     torch.cuda.synchronize()
     assert_attn_close(host_bits(out), ref_o)
     assert_lse_close(lse.cpu().numpy(), ref_l)
+
+
+@pytest.mark.parametrize("R,Hq,T,B,ks", [(13, 32, 5, 16, 128), (25, 32, 1, 32, 64), (32, 64, 5, 32, 64)])
+def test_attn_past_the_caches(R, Hq, T, B, ks):
+    """Calls over 96 MB take the non-temporal loads (both split kernels; B = 32 with the CUs full for the many-row
+    one), against the oracle on the first and the last request."""
+    Hkv = 8
+    g = torch.Generator(device="cuda").manual_seed(R)
+    shape = (R, ks + 1, Hkv, B, 128)
+    pk = torch.randn(shape, generator=g, device="cuda", dtype=torch.bfloat16)
+    pv = torch.randn((R, ks + 1, Hkv, 128, B), generator=g, device="cuda", dtype=torch.bfloat16)
+    q = torch.randn((R, T, Hq, 128), generator=g, device="cuda", dtype=torch.bfloat16)
+    smap = torch.arange(ks, dtype=torch.int32, device="cuda").expand(R, Hkv, ks).contiguous()
+    ctx = torch.full((R,), (ks + 1) * B - 3, dtype=torch.int32, device="cuda")
+    assert pk.numel() * 4 > 96 << 20
+    d = P.dims(R, Hq, Hkv, 128, B, ks + 2)
+    out, lse = torch.empty_like(q), torch.empty((R, T, Hq), device="cuda")
+    ws = torch.zeros(max(1, P.oasis_attn_workspace_bytes(d, T, ks)), dtype=torch.uint8, device="cuda")
+    note(f"attn past the caches R={R} Hq={Hq} T={T} B={B} ks={ks}")
+    P.oasis_sparse_decode_attn(d, q, T, pk, pv, smap, ks, ctx, None, out, lse, ws)
+    torch.cuda.synchronize()
+    for r in (0, R - 1):
+        bits = [host_bits(x[r:r + 1]) for x in (q, pk, pv)]
+        ref_o, ref_l = O.sparse_attend(bits[0], bits[1], np.ascontiguousarray(np.swapaxes(bits[2], -1, -2)),
+                                       smap[r:r + 1].cpu().numpy(), ctx[r:r + 1].cpu().numpy(), B)
+        assert_attn_close(host_bits(out[r:r + 1]), ref_o)
+        assert_lse_close(lse[r:r + 1].cpu().numpy(), ref_l)
+
+
+def test_summaries_and_scores_past_the_caches():
+    """The non-temporal forms of the summaries (from 192 MB of keys) and of the vector-ALU scorer (from 96 MB)
+    against torch's extrema (exact) and the 64-bit bound (fp32 sums: 1e-5 of the score, 1e-3)."""
+    R, H, NB, B = 7, 8, 7000, 16
+    g = torch.Generator(device="cuda").manual_seed(5)
+    pages = torch.randn((R * NB, H, B, 128), generator=g, device="cuda", dtype=torch.bfloat16)
+    table = torch.randperm(R * NB, generator=g, device="cuda").to(torch.int32).view(R, NB).contiguous()
+    ctx = torch.tensor([NB * B - 5 - 1000 * r for r in range(R)], dtype=torch.int32, device="cuda")
+    kmax = torch.zeros((R, H, NB, 128), dtype=torch.bfloat16, device="cuda")
+    kmin = torch.zeros_like(kmax)
+    d = P.dims(R, H, H, 128, B, NB)
+    q = torch.randn((R, 2, H, 128), generator=g, device="cuda", dtype=torch.bfloat16)
+    scores = torch.empty((R, H, NB), device="cuda")
+    note("summaries and scores past the caches")
+    P.oasis_build_summaries(d, pages, table, ctx, kmax, kmin)
+    P.oasis_score_blocks(d, q, 2, 1, 1, kmax, kmin, ctx, scores)
+    torch.cuda.synchronize()
+    for r in (0, 3, R - 1):
+        nc = (int(ctx[r]) + B - 1) // B - 1
+        keys = pages[table[r, :nc].long()]
+        for got, want in ((kmax, keys.amax(2)), (kmin, keys.amin(2))):
+            assert torch.equal(got[r, :, :nc], want.transpose(0, 1)) and not got[r, :, nc:].any()
+        qd = q[r, 1].double()[:, None, :]
+        ref = torch.maximum(qd * kmax[r, :, :nc].double(), qd * kmin[r, :, :nc].double()).sum(-1)
+        assert torch.all((scores[r, :, :nc].double() - ref).abs() <= 1e-3 + 1e-5 * ref.abs())
+        assert torch.all(scores[r, :, nc:] == -float("inf"))
