@@ -57,7 +57,7 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // in one L2, the heads of a request, whose slots are adjacent in the pools,
 // share its XCD, and any number of pairs spreads over all XCDs. (Pairs dealt
 // modulo 8, as before: 90 requests x 8 KV heads, 761 MB, 143 against 124 us a
-// call; 64 x 8, 544 MB, 103 and 94 us.) With fewer than 8 pairs each takes an
+// call, 116 with V past the caches; 64 x 8, 544 MB, 103 and 94.) With fewer than 8 pairs each takes an
 // XCD of its own, so that its merge reads the partials from the L2 that holds
 // them (1 pair: 9.3 us, spread over the XCDs 10.2). Returns -1 past the last item.
 __device__ __forceinline__ int xcd_item(int wg, int pairs, int parts) {
@@ -268,8 +268,8 @@ __device__ __forceinline__ uint64_t map_mask(int ks, int slot, int entry) {
 // Units whose slots are all free are not read: the first two units of a wave
 // are loaded before the slot map has arrived, every later one is the next unit
 // with an attended slot. At 64 requests x 8 KV heads with contexts of 200 to
-// 3,000 tokens in 128-slot pools (383 of 541 MB attended) a call takes 74 us,
-// against 104 us when every slot is read. Every unit's addresses are a
+// 3,000 tokens in 128-slot pools (383 of 541 MB attended) a call takes 75.7 us
+// (71.4 with V past the caches), against 104 when every slot is read. Every unit's addresses are a
 // wave-uniform base and a 32-bit lane offset (UnitOffsets); 64-bit vector
 // addresses took 17.9 against 16.9 us at 8 x 131,072 tokens (68 MB).
 template <int NT, int BS, bool STREAM>
@@ -507,7 +507,7 @@ __global__ __launch_bounds__(kW * 64) void attn_split_kernel(AttnArgs a) {
 // rows (B = 16, 2,048-token budget, 189 MB) 68 us with one team, 45 us with two;
 // 25 requests at B = 32 and budget 4,096 (429 MB) 109 and 83 us; 16 x 65,536
 // tokens (B = 32, 72 rows, 274 MB; two splits per head and a merge) 63 and
-// 61 us. Three or four teams (two stages fit) 62.9 us at the last, four stages
+// 61 us (with plain loads, as the figures below; 53.3 past the caches). Three or four teams (two stages fit) 62.9 us at the last, four stages
 // 62.0, two 63.7. Each team's operands of a unit are read together and then
 // used: reading a K chunk, waiting and reading the next took 47 us at the first.
 // Short splits pay for the second team's part of the merge: 16 pairs in 15

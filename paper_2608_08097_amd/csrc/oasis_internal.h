@@ -210,7 +210,7 @@ hipError_t launch_stage(const StageArgs& a, hipStream_t s, const LaunchTiming& t
 // the transfer plan when `plan` is set (mode kStagePlanOnly, into plan->ws).
 // Scores and selections are identical to launch_score followed by launch_topk.
 // For 5 to kScoreSelectMaxRows scoring rows (more would not fit the registers of
-// a 1024-thread workgroup) and at most kScoreSelectMaxBlocks blocks per row.
+// a 512-thread workgroup) and at most kScoreSelectMaxBlocks blocks per row.
 constexpr int kScoreSelectMaxRows = 32;
 constexpr int kScoreSelectMaxBlocks = 16384;
 bool score_select_supported(const ScoreArgs& sa);

@@ -25,7 +25,7 @@ constexpr int kQ = 0, kPred = 1, kAttn = 2, kJoinPred = 3, kJoinXfer = 4, kStage
 constexpr uint32_t kWrapGuard = 1u << 30;
 constexpr int kProfKinds = 4;  // attention (split + merge), scoring, top-K, staging
 // (request, KV head) pairs from which OASIS_FUSED_PREDICTION_AUTO scores and
-// selects in one kernel (one 1024-thread workgroup per pair: a full chip)
+// selects in one kernel (one 512-thread workgroup per pair: a full chip)
 constexpr long long kFusedMinPairs = 256;
 // (request, KV head) pairs up to which OASIS_PREDICT_AUTO starts the prediction
 // after the attention (measured on MI355X, steps/s beside / after: 1 pair x
