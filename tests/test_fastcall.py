@@ -125,3 +125,15 @@ def test_capture_takes_the_current_stream():
         torch.cuda.synchronize()
         for n in ("scores", "sel", "cnt", "out", "lse", "smap", "pool_k"):
             assert torch.equal(t[n], ref[n]), n
+
+
+def test_module_has_no_thread_local_storage():
+    """Loading a module with a TLS segment slows every thread_local access of the libraries loaded before it."""
+    import struct
+    import paper_2608_08097_amd._fastcall as fast
+    with open(fast.__file__, "rb") as f:
+        head = f.read(64)
+        off, size, count = struct.unpack_from("<Q", head, 32)[0], *struct.unpack_from("<HH", head, 54)
+        f.seek(off)
+        types = [struct.unpack_from("<I", f.read(size))[0] for _ in range(count)]
+    assert 1 in types and 7 not in types  # PT_LOAD, PT_TLS
