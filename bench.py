@@ -67,7 +67,7 @@ def measured_traffic(kind):
     key = {"score": ("score_kernel_traffic_bytes", "score_sources_sha256"),
            "attention": ("attention_traffic_bytes", "attn_sources_sha256")}[kind]
     files = {"score": ("score.hip", "score_core.h", "oasis_internal.h"),
-             "attention": ("attn.hip", "oasis_internal.h")}[kind]
+             "attention": ("attn.hip", "attn_plan.h", "oasis_internal.h")}[kind]
     try:
         note = open(TRAFFIC_NOTE).read()
         h = hashlib.sha256()

@@ -178,7 +178,7 @@ oasis_status make_stage_args(const oasis_dims* dims, const uint16_t* host_k, con
 oasis_status make_attn_args(const oasis_dims* dims, const uint16_t* q, int32_t num_q_tokens, const uint16_t* pool_k,
                             const uint16_t* pool_v, const int32_t* slot_map, int32_t k_slots, const int32_t* ctx_len,
                             float scale, uint16_t* out, float* lse, void* workspace, size_t workspace_bytes,
-                            AttnArgs* a, const char* fn) {
+                            AttnArgs* a, const char* fn, int busy) {
   oasis_status st = check_dims(dims, fn);
   if (st != OASIS_OK) return st;
   if (num_q_tokens < 1) return fail(OASIS_ERR_INVALID_ARG, "%s: num_q_tokens < 1", fn);
@@ -196,7 +196,7 @@ oasis_status make_attn_args(const oasis_dims* dims, const uint16_t* q, int32_t n
   REQUIRE_PTR(out, fn);
   if (k_slots > 0) REQUIRE_PTR(slot_map, fn);
   const AttnPlan p = attn_plan(dims->num_reqs, dims->num_q_heads, dims->num_kv_heads, num_q_tokens,
-                               dims->block_size, k_slots);
+                               dims->block_size, k_slots, busy);
   if (p.bytes > 0 && (!workspace || workspace_bytes < p.bytes))
     return fail(OASIS_ERR_WORKSPACE, "%s: workspace of %zu bytes, %zu needed", fn, workspace_bytes, p.bytes);
   AttnArgs t{};

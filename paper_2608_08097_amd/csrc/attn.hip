@@ -41,13 +41,6 @@
 namespace oasis {
 namespace {
 
-constexpr int kW = 4;  // waves per workgroup
-// Workgroups of one attention call: one per CU (the register-prefetching
-// kernel of up to two row tiles holds one wave per SIMD; the many-row kernel
-// one workgroup of up to ten waves per CU).
-constexpr int kTargetWorkgroups = 256;
-constexpr int kMaxSplits = 16;
-
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // XCD-aware placement of the `parts` items of each (request, KV head) pair:
@@ -966,48 +959,6 @@ hipError_t launch_bs(const AttnArgs& a, hipStream_t s, const LaunchTiming& t) {
 }
 
 }  // namespace
-
-AttnPlan attn_plan(int R, int Hq, int Hkv, int T, int B, int k_slots) {
-  AttnPlan p{};
-  const int G = Hq / Hkv;
-  p.rows = G * T;
-  p.n_units = B == 16 ? (k_slots + 2) / 2 : k_slots + 1;
-  const long long nrh = (long long)R * Hkv;
-  // `want` splits of at least `least` units each, at most kMaxSplits
-  auto split = [&](long long want, int least) {
-    const long long most = (p.n_units + least - 1) / least;
-    want = want < most ? want : most;
-    want = want < kMaxSplits ? want : kMaxSplits;
-    want = want > 1 ? want : 1;
-    p.units_per_split = (int)((p.n_units + want - 1) / want);
-    p.nsplit = (p.n_units + p.units_per_split - 1) / p.units_per_split;
-  };
-  // The workspace holds the partials of the smallest split that gives every CU
-  // a workgroup and every wave a unit, the finest split that can pay.
-  long long want = (kTargetWorkgroups + nrh - 1) / (nrh > 0 ? nrh : 1);
-  split(want, kW);
-  p.bytes = p.nsplit > 1 ? (size_t)nrh * p.nsplit * p.rows * (kHeadDim + 2) * sizeof(float) : 0;
-  // The split launched is the largest that needs no second round of workgroups:
-  // a CU holds one workgroup (of up to two row tiles: one wave per SIMD), so a
-  // few workgroups more than CUs take a round of their own. Measured on MI355X
-  // (8 KV heads, 20 rows, budget 2,048), smallest split that fills against this
-  // one: 3 requests 17.3 against 12.8 us, 5 requests 18.1 and 13.0, 17 requests
-  // 43.0 and 33.6, 22 requests (two splits against one, no merge) 46.3 and 35.5.
-  if (p.nsplit > 1 && nrh * p.nsplit > kTargetWorkgroups) want = kTargetWorkgroups / nrh;
-  split(want, p.rows <= 32 ? kW : 6);
-  // Fewer splits where no wave's chain gets longer: 65 units in 13 splits of 5
-  // leave one wave of four with two units, and so do 9 splits of 8 (1 request x 8
-  // KV heads, 20 rows, per call: 10.8 and 10.5 us; 2 requests 12.1 and 11.4 us).
-  // One row tile has little to merge (8.3 against 8.5 us), and the many-row
-  // kernel's two teams take at least three units each (72 rows: 14.1 -> 13.6 us).
-  if (p.rows > 16 && p.rows <= 32 && p.nsplit > 1) {
-    const int depth = (p.units_per_split + kW - 1) / kW;
-    split((p.n_units + depth * kW - 1) / (depth * kW), kW);
-  }
-  // partials exist only with several splits (one split writes the outputs itself)
-  p.part_o_floats = p.nsplit > 1 ? (size_t)nrh * p.nsplit * p.rows * kHeadDim : 0;
-  return p;
-}
 
 hipError_t launch_attn(const AttnArgs& a, hipStream_t s, const LaunchTiming& t) {
   return a.B == 16 ? launch_bs<16>(a, s, t) : launch_bs<32>(a, s, t);

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "attn_plan.h"
 #include "oasis.h"
 
 namespace oasis {
@@ -13,7 +14,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kHeadDim = 128;
 constexpr int kWave = 64;
 
 // --- small device helpers ---------------------------------------------------
@@ -206,6 +206,8 @@ inline size_t stage_ws_ints(long long nrh, int k) { return (size_t)nrh * (4 * (s
 // kernel; a.mode must be kStagePlanOnly (the plan goes to a.ws).
 hipError_t launch_topk_plan(const TopkArgs& t, const StageArgs& a, hipStream_t s, const LaunchTiming& lt = {});
 hipError_t launch_stage(const StageArgs& a, hipStream_t s, const LaunchTiming& t = {});
+// Workgroups of a delta transfer of nrh (request, KV head) pairs; each has a CU's LDS nearly to itself.
+int stage_workgroups(int B, int nrh);
 // Scoring and top-K of each (request, KV head) in one workgroup (stage.hip), with
 // the transfer plan when `plan` is set (mode kStagePlanOnly, into plan->ws).
 // Scores and selections are identical to launch_score followed by launch_topk.
@@ -231,11 +233,6 @@ struct AttnArgs {
   float scale_log2;         // scale * log2(e)
   int rows, n_units, nsplit, units_per_split;
 };
-struct AttnPlan {
-  int rows, n_units, nsplit, units_per_split;
-  size_t part_o_floats, bytes;  // bytes: what oasis_attn_workspace_bytes returns
-};
-AttnPlan attn_plan(int R, int Hq, int Hkv, int T, int B, int k_slots);
 hipError_t launch_attn(const AttnArgs& a, hipStream_t s, const LaunchTiming& t = {});
 // Scratch of oasis_sparse_decode_attn_noalloc: a device array of this many bytes
 // per GPU (attn.hip); noalloc_scratch returns its address on the current device.
@@ -269,6 +266,6 @@ oasis_status make_stage_args(const oasis_dims* dims, const uint16_t* host_k, con
 oasis_status make_attn_args(const oasis_dims* dims, const uint16_t* q, int32_t num_q_tokens, const uint16_t* pool_k,
                             const uint16_t* pool_v, const int32_t* slot_map, int32_t k_slots, const int32_t* ctx_len,
                             float scale, uint16_t* out, float* lse, void* workspace, size_t workspace_bytes,
-                            AttnArgs* a, const char* fn);
+                            AttnArgs* a, const char* fn, int busy = 0);
 
 }  // namespace oasis

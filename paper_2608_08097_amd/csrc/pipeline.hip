@@ -5,7 +5,9 @@
 //
 // Host code only: every step builds the kernel arguments with the checks the
 // single-call entry points use and launches the same kernels, so a pipelined
-// step computes exactly what the sequence of entry-point calls computes.
+// step computes what the sequence of entry-point calls computes. (Attention of
+// more than 32 rows may be cut into fewer splits than the single call, since
+// the staging workgroups hold CUs: the sums are then rounded in another order.)
 //
 // Cross-stream edges are monotone 32-bit counters in a small device array
 // (hipStreamWriteValue32 after the producer's work, hipStreamWaitValue32 >=
@@ -361,7 +363,8 @@ oasis_status oasis_pipeline_step(oasis_pipeline* p, int32_t layer, const uint16_
   oasis::StageArgs ga{}, la{};
   oasis_status st;
   if ((st = oasis::make_attn_args(d, q, p->T, b.pool_k, b.pool_v, b.slot_map, p->k, ctx_len, p->scale, b.out,
-                                  b.lse, b.workspace, b.workspace_bytes, &aa, fn)) != OASIS_OK)
+                                  b.lse, b.workspace, b.workspace_bytes, &aa, fn,
+                                  oasis::stage_workgroups(d->block_size, d->num_reqs * d->num_kv_heads))) != OASIS_OK)
     return st;
   if ((st = oasis::make_score_args(d, q, p->T, p->first_draft, p->num_draft, b.kmax, b.kmin, ctx_len, b.scores,
                                    &sa, fn)) != OASIS_OK)

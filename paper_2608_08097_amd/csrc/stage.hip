@@ -1137,17 +1137,20 @@ hipError_t launch_score_select(const ScoreArgs& sa, const TopkArgs& t, const Sta
                                                : launch_score_select_nrt<2>(sa, t, plan, s, lt);
 }
 
+int stage_workgroups(int B, int nrh) {
+  // B = 16: kCopyWorkgroups; B = 32 (16 KiB entries, twice the stores and
+  // transposes per entry): one workgroup per two pairs, up to twice as many
+  int grid = B == 16 ? kCopyWorkgroups : nrh / 2;
+  grid = grid < kCopyWorkgroups ? kCopyWorkgroups : (grid > 2 * kCopyWorkgroups ? 2 * kCopyWorkgroups : grid);
+  return grid < nrh ? grid : nrh;
+}
+
 template <int BS>
 hipError_t launch_bs(const StageArgs& a, hipStream_t s, const LaunchTiming& t) {
   const int nrh = a.R * a.Hkv;
   if (nrh <= 0) return hipSuccess;
-  // B = 16: kCopyWorkgroups; B = 32 (16 KiB entries, twice the stores and
-  // transposes per entry): one workgroup per two pairs, up to twice as many
-  int grid = BS == 16 ? kCopyWorkgroups : nrh / 2;
-  grid = grid < kCopyWorkgroups ? kCopyWorkgroups : (grid > 2 * kCopyWorkgroups ? 2 * kCopyWorkgroups : grid);
   // the local block alone (no plan, one entry per pair, on the caller's critical path): spread wide
-  if (a.local_only) grid = nrh < kLocalWorkgroups ? nrh : kLocalWorkgroups;
-  if (grid > nrh) grid = nrh;
+  const int grid = !a.local_only ? stage_workgroups(BS, nrh) : nrh < kLocalWorkgroups ? nrh : kLocalWorkgroups;
   // entries per batch; two batches are in flight per workgroup
   const int pf = grid * 2 >= kCopyInflightMin ? 1 : kCopyInflightMin / (2 * grid);
   if (pf >= 8)
