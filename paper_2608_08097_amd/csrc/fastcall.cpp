@@ -16,6 +16,7 @@
 
 #include <cmath>
 #include <cstdint>
+#include <initializer_list>
 
 #include "oasis.h"
 
@@ -38,15 +39,27 @@ bool dtype_is(at::ScalarType t, Kind k) {
   }
 }
 
-// The data of a plain contiguous tensor of n elements (n < 0: any count), on the
-// device or, where pinned memory is allowed, pinned; false: not such a tensor.
-bool tensor(PyObject* o, int64_t n, Kind kind, void** p, bool pinned_ok = false) {
+// Product of counts; -1, which no tensor matches, with a negative factor or past 63 bits.
+int64_t count(std::initializer_list<int64_t> factors) {
+  int64_t n = 1;
+  bool bad = false;
+  for (const int64_t f : factors) bad |= f < 0 || __builtin_mul_overflow(n, f, &n);
+  return bad ? -1 : n;
+}
+
+// The data of a plain contiguous tensor on the device or, where pinned memory is
+// allowed, pinned; false: not such a tensor.
+bool any_count(PyObject* o, Kind kind, void** p, bool pinned_ok = false) {
   if (!THPVariable_CheckExact(o)) return false;
   const at::Tensor& t = THPVariable_Unpack(o);
-  if ((n >= 0 && t.numel() != n) || !dtype_is(t.scalar_type(), kind) || !t.is_contiguous()) return false;
+  if (!dtype_is(t.scalar_type(), kind) || !t.is_contiguous()) return false;
   if (!t.is_cuda() && !(pinned_ok && t.is_pinned())) return false;
   *p = t.data_ptr();
   return true;
+}
+// The same, of exactly n elements.
+bool tensor(PyObject* o, int64_t n, Kind kind, void** p, bool pinned_ok = false) {
+  return THPVariable_CheckExact(o) && THPVariable_Unpack(o).numel() == n && any_count(o, kind, p, pinned_ok);
 }
 
 bool int32(PyObject* o, int32_t* v) {
@@ -105,16 +118,18 @@ PyObject* sparse_decode_attn(PyObject*, Args a, Py_ssize_t n) {
     const oasis_dims* d = dims_at(a[0]);
     int32_t T, k;
     if (!d || !int32(a[2], &T) || !int32(a[6], &k)) FALLBACK;
-    const int64_t R = d->num_reqs, H = d->num_kv_heads, D = d->head_dim, rows = R * T * d->num_q_heads;
-    const int64_t pool = R * ((int64_t)k + 1) * H * d->block_size * D;
+    const int64_t R = d->num_reqs, H = d->num_kv_heads, D = d->head_dim;
+    const int64_t rows = count({R, T, d->num_q_heads}), qn = count({R, T, d->num_q_heads, D});
+    const int64_t pool = count({R, (int64_t)k + 1, H, d->block_size, D});
     void *q, *pk, *pv, *map, *ctx, *out, *lse = nullptr, *ws, *s;
     float scale;
+    if (D <= 0) FALLBACK;  // no default scale
     if (a[8] == Py_None) scale = (float)(1.0 / std::sqrt((double)D));
     else if (PyFloat_CheckExact(a[8])) scale = (float)PyFloat_AS_DOUBLE(a[8]);
     else FALLBACK;
-    if (!tensor(a[1], rows * D, kBf16, &q) || !tensor(a[3], pool, kBf16, &pk) || !tensor(a[4], pool, kBf16, &pv) ||
-        !tensor(a[5], R * H * k, kI32, &map) || !tensor(a[7], R, kI32, &ctx) || !tensor(a[9], rows * D, kBf16, &out) ||
-        (a[10] != Py_None && !tensor(a[10], rows, kF32, &lse)) || !tensor(a[11], -1, kU8, &ws) ||
+    if (!tensor(a[1], qn, kBf16, &q) || !tensor(a[3], pool, kBf16, &pk) || !tensor(a[4], pool, kBf16, &pv) ||
+        !tensor(a[5], count({R, H, k}), kI32, &map) || !tensor(a[7], R, kI32, &ctx) || !tensor(a[9], qn, kBf16, &out) ||
+        (a[10] != Py_None && !tensor(a[10], rows, kF32, &lse)) || !any_count(a[11], kU8, &ws) ||
         !stream_at(a[12], &s))
       FALLBACK;
     const size_t bytes = (size_t)THPVariable_Unpack(a[11]).numel();
@@ -132,10 +147,11 @@ struct Score {
 // q, num_q_tokens, first_draft, num_draft, kmax, kmin, ctx_len at a[1..7]; scores at a[scores]
 bool score_args(const oasis_dims* d, Args a, int scores, Score* s) {
   if (!d || !int32(a[2], &s->T) || !int32(a[3], &s->first) || !int32(a[4], &s->num)) return false;
-  const int64_t R = d->num_reqs, rows = R * d->num_kv_heads * (int64_t)d->max_blocks, D = d->head_dim;
-  return tensor(a[1], R * s->T * d->num_q_heads * D, kBf16, &s->q) && tensor(a[5], rows * D, kBf16, &s->kmax) &&
-         tensor(a[6], rows * D, kBf16, &s->kmin) && tensor(a[7], R, kI32, &s->ctx) &&
-         tensor(a[scores], rows, kF32, &s->scores);
+  const int64_t R = d->num_reqs, H = d->num_kv_heads, NB = d->max_blocks, D = d->head_dim;
+  const int64_t summary = count({R, H, NB, D});
+  return tensor(a[1], count({R, s->T, d->num_q_heads, D}), kBf16, &s->q) && tensor(a[5], summary, kBf16, &s->kmax) &&
+         tensor(a[6], summary, kBf16, &s->kmin) && tensor(a[7], R, kI32, &s->ctx) &&
+         tensor(a[scores], count({R, H, NB}), kF32, &s->scores);
 }
 
 // dims, q, num_q_tokens, first_draft, num_draft, kmax, kmin, ctx_len, scores, stream
@@ -161,9 +177,9 @@ PyObject* select_topk(PyObject*, Args a, Py_ssize_t n) {
     int32_t k;
     void *scores, *ctx, *sel, *cnt, *s;
     if (!d || !int32(a[3], &k)) FALLBACK;
-    const int64_t R = d->num_reqs, RH = R * d->num_kv_heads;
-    if (!tensor(a[1], RH * d->max_blocks, kF32, &scores) || !tensor(a[2], R, kI32, &ctx) ||
-        !tensor(a[4], RH * k, kI32, &sel) || !tensor(a[5], RH, kI32, &cnt) || !stream_at(a[6], &s))
+    const int64_t R = d->num_reqs, RH = count({R, d->num_kv_heads});
+    if (!tensor(a[1], count({RH, d->max_blocks}), kF32, &scores) || !tensor(a[2], R, kI32, &ctx) ||
+        !tensor(a[4], count({RH, k}), kI32, &sel) || !tensor(a[5], RH, kI32, &cnt) || !stream_at(a[6], &s))
       FALLBACK;
     return run([&] {
       return f_topk(d, (const float*)scores, (const int32_t*)ctx, k, (int32_t*)sel, (int32_t*)cnt, s);
@@ -180,8 +196,8 @@ PyObject* score_select(PyObject*, Args a, Py_ssize_t n) {
     int32_t k;
     void *sel, *cnt, *s;
     if (!score_args(d, a, 9, &c) || !int32(a[8], &k)) FALLBACK;
-    const int64_t RH = (int64_t)d->num_reqs * d->num_kv_heads;
-    if (!tensor(a[10], RH * k, kI32, &sel) || !tensor(a[11], RH, kI32, &cnt) || !stream_at(a[12], &s)) FALLBACK;
+    const int64_t RH = count({d->num_reqs, d->num_kv_heads});
+    if (!tensor(a[10], count({RH, k}), kI32, &sel) || !tensor(a[11], RH, kI32, &cnt) || !stream_at(a[12], &s)) FALLBACK;
     return run([&] {
       return f_score_select(d, (const uint16_t*)c.q, c.T, c.first, c.num, (const uint16_t*)c.kmax,
                             (const uint16_t*)c.kmin, (const int32_t*)c.ctx, k, (float*)c.scores, (int32_t*)sel,
@@ -200,14 +216,15 @@ PyObject* stage_blocks(PyObject*, Args a, Py_ssize_t n) {
     if (!d || !int32(a[3], &pages) || !int32(a[9], &k) || !int32(a[12], &step) || !int32(a[13], &cap) ||
         (a[14] != Py_True && a[14] != Py_False))
       FALLBACK;
-    const int64_t R = d->num_reqs, RH = R * d->num_kv_heads, entry = (int64_t)d->block_size * d->head_dim;
-    const int64_t tier = pages * (int64_t)d->num_kv_heads * entry, pool = RH * ((int64_t)k + 1) * entry;
+    const int64_t R = d->num_reqs, H = d->num_kv_heads, RH = count({R, H});
+    const int64_t tier = count({pages, H, d->block_size, d->head_dim});
+    const int64_t pool = count({RH, (int64_t)k + 1, d->block_size, d->head_dim}), items = count({RH, k});
     void *hk, *hv, *table, *ctx, *sel, *cnt, *scores, *map, *stamp, *pk, *pv, *moved, *s;
     if (!tensor(a[1], tier, kBf16, &hk, true) || !tensor(a[2], tier, kBf16, &hv, true) ||
-        !tensor(a[4], R * d->max_blocks, kI32, &table) || !tensor(a[5], R, kI32, &ctx) ||
-        !tensor(a[6], RH * k, kI32, &sel) || !tensor(a[7], RH, kI32, &cnt) ||
-        !tensor(a[8], RH * d->max_blocks, kF32, &scores) || !tensor(a[10], RH * k, kI32, &map) ||
-        !tensor(a[11], RH * k, kI32, &stamp) || !tensor(a[15], pool, kBf16, &pk) ||
+        !tensor(a[4], count({R, d->max_blocks}), kI32, &table) || !tensor(a[5], R, kI32, &ctx) ||
+        !tensor(a[6], items, kI32, &sel) || !tensor(a[7], RH, kI32, &cnt) ||
+        !tensor(a[8], count({RH, d->max_blocks}), kF32, &scores) || !tensor(a[10], items, kI32, &map) ||
+        !tensor(a[11], items, kI32, &stamp) || !tensor(a[15], pool, kBf16, &pk) ||
         !tensor(a[16], pool, kBf16, &pv) || !tensor(a[17], RH, kI32, &moved) || !stream_at(a[18], &s))
       FALLBACK;
     const int32_t copy_local = a[14] == Py_True;

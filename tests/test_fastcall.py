@@ -107,6 +107,79 @@ def test_checks_and_results_match_the_python_binding():
         assert all(torch.equal(x, y) for x, y in zip(outs[0], other))
 
 
+def _calls(t, host_k, host_v):
+    """The five native functions with plain arguments, without the stream."""
+    d = ctypes.addressof(t["d"])
+    return {
+        "score_blocks": [d, t["q"], T, 1, T - 1, t["kmax"], t["kmin"], t["ctx"], t["scores"]],
+        "select_topk": [d, t["scores"], t["ctx"], K, t["sel"], t["cnt"]],
+        "score_select": [d, t["q"], T, 1, T - 1, t["kmax"], t["kmin"], t["ctx"], K, t["scores"], t["sel"], t["cnt"]],
+        "stage_blocks": [d, host_k, host_v, host_k.shape[0], t["table"], t["ctx"], t["sel"], t["cnt"], t["scores"], K,
+                         t["smap"], t["stamp"], 1, K, True, t["pool_k"], t["pool_v"], t["moved"]],
+        "sparse_decode_attn": [d, t["q"], T, t["pool_k"], t["pool_v"], t["smap"], K, t["ctx"], 0.5, t["out"], t["lse"],
+                               t["ws"]],
+    }
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tier", ["device", "pinned"])
+def test_plain_calls_are_accepted(tier):
+    """Every function takes the plain call itself (status 0, not None, which would be the Python binding's turn),
+    on the current stream and on a handle, and leaves what the Python binding leaves."""
+    L.lib()
+    side = torch.cuda.Stream()
+    outs = []
+    for stream in ("python", None, side.cuda_stream):
+        t = _tensors("cuda")
+        host = [t[n] if tier == "device" else t[n].cpu().pin_memory() for n in ("host_k", "host_v")]
+        torch.cuda.synchronize()
+        keep = L._fast
+        L._fast = None if stream == "python" else keep
+        try:
+            for name, args in _calls(t, *host).items():
+                if stream == "python":
+                    getattr(P, "oasis_" + name)(t["d"], *(args[1:3] + args[4:] if name == "stage_blocks" else args[1:]))
+                else:
+                    assert getattr(keep, name)(*args, stream) == 0, name
+        finally:
+            L._fast = keep
+        torch.cuda.synchronize()
+        outs.append([t[n].clone() for n in ("scores", "sel", "cnt", "smap", "stamp", "pool_k", "pool_v", "moved",
+                                            "out", "lse")])
+    for other in outs[1:]:
+        assert all(torch.equal(x, y) for x, y in zip(outs[0], other))
+
+
+@pytest.mark.gpu
+def test_bad_counts_keep_the_bindings_errors():
+    """Negative and overflowing counts match no tensor: the Python binding refuses them as it always did, before
+    the library is called (in the native functions a negative product used to mean any count)."""
+    L.lib()
+    t = _tensors("cuda")
+    host = t["host_k"], t["host_v"]
+    at = {"score_blocks": (2,), "select_topk": (3,), "score_select": (2, 8), "stage_blocks": (3, 9),
+          "sparse_decode_attn": (2, 6)}
+    for name, places in at.items():
+        for i in places:
+            for bad in (-1, -2, -(1 << 31), (1 << 31) - 1):
+                args = _calls(t, *host)[name]
+                args[i] = bad
+                assert getattr(L._fast, name)(*args, None) is None, (name, i, bad)
+    for bad in (-1, -2):
+        with pytest.raises(ValueError, match="sel: "):
+            P.oasis_select_topk(t["d"], t["scores"], t["ctx"], bad, t["sel"], t["cnt"])
+        with pytest.raises(ValueError, match="q: "):
+            P.oasis_score_blocks(t["d"], t["q"], bad, 1, 2, t["kmax"], t["kmin"], t["ctx"], t["scores"])
+    # 2^30 requests of 2^30 heads and 16 tokens: 2^64 rows are not the 0 rows of an empty tensor
+    huge = P.dims(1 << 30, 1 << 30, 1, 128, B, NB)
+    empty = t["q"][:0]
+    call = [ctypes.addressof(huge), empty, 16, empty, empty, t["sel"][:0], 0, t["ctx"], None, empty, None, t["ws"], None]
+    assert L._fast.sparse_decode_attn(*call) is None
+    none = P.dims(R, H * G, H, 0, B, NB)  # no head dimension: the default scale does not exist
+    with pytest.raises(ZeroDivisionError):
+        P.oasis_sparse_decode_attn(none, empty, T, empty, empty, t["smap"], K, t["ctx"], None, empty, None, t["ws"])
+
+
 @pytest.mark.gpu
 def test_capture_takes_the_current_stream():
     """A captured step replays on its own stream and gives the eager results, replay after replay."""
