@@ -10,13 +10,15 @@ first call raises.
 The calls a decode step makes many times first go to ``_fastcall`` (built
 beside the library), which makes the same checks and the call natively and
 returns None for arguments it does not accept as they are; those, and every
-error, take the Python code below it.
+error, take the Python code below it. So does every call, with a warning when
+the library is loaded, where ``_fastcall`` is missing or does not fit.
 """
 from __future__ import annotations
 
 import ctypes
 import math
 import os
+import warnings
 
 import torch
 
@@ -66,7 +68,8 @@ def dims(num_reqs, num_q_heads, num_kv_heads, head_dim, block_size, max_blocks) 
 
 
 _lib = None
-_fast = None  # the _fastcall module, bound to the loaded library
+_fast = None  # the _fastcall module, bound to the loaded library (None: calls are marshalled in Python)
+_BUILD_HINT = "Build it with __graft_entry__.build() or python -m paper_2608_08097_amd.build_lib"
 ABI_VERSION = 7  # OASIS_ABI_VERSION of include/oasis.h
 
 _P = ctypes.c_void_p
@@ -81,8 +84,7 @@ def lib() -> ctypes.CDLL:
     global _lib
     if _lib is None:
         if not os.path.exists(LIB_PATH):
-            raise RuntimeError(f"{LIB_PATH} is missing: build it with __graft_entry__.build() "
-                               "or python -m paper_2608_08097_amd.build_lib")
+            raise RuntimeError(f"{LIB_PATH} is missing. {_BUILD_HINT}")
         L = ctypes.CDLL(LIB_PATH)
         L.oasis_last_error.restype = ctypes.c_char_p
         L.oasis_last_error.argtypes = []
@@ -149,14 +151,32 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
-def _bind_fast(L: ctypes.CDLL) -> None:
-    """Point the native marshalling at the entry points of the loaded library."""
-    global _fast
+def _load_fast():
     from . import _fastcall
-    _fastcall.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+    return _fastcall
+
+
+def _bind_fast(L: ctypes.CDLL) -> None:
+    """Point the native marshalling at the entry points of the loaded library. Without a module that fits it
+    (not built, built for another PyTorch, or left over from another ABI version) every call is marshalled by
+    the Python code below: the same kernels and results, some microseconds more of host time a call."""
+    global _fast
+    _fast = None
+    try:
+        fast = _load_fast()
+        built_for = fast.abi_version
+    except (ImportError, AttributeError) as e:
+        warnings.warn(f"native marshalling not loaded ({e}): calls go through the slower Python binding. {_BUILD_HINT}",
+                      RuntimeWarning, stacklevel=2)
+        return
+    if built_for != ABI_VERSION:
+        warnings.warn(f"{fast.__file__} was built for ABI version {built_for}, the library has {ABI_VERSION}: calls "
+                      f"go through the slower Python binding. {_BUILD_HINT}", RuntimeWarning, stacklevel=2)
+        return
+    fast.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
         L.oasis_sparse_decode_attn, L.oasis_score_blocks, L.oasis_select_topk, L.oasis_score_select,
         L.oasis_stage_blocks)))
-    _fast = _fastcall
+    _fast = fast
 
 
 def _handle(stream):

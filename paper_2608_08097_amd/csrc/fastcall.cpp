@@ -259,4 +259,9 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fastcall", nullptr, -1, methods, 
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__fastcall(void) { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__fastcall(void) {
+  PyObject* m = PyModule_Create(&module);
+  // the signatures the calls above were compiled with; the binding compares it with the loaded library's
+  if (m && PyModule_AddIntConstant(m, "abi_version", OASIS_ABI_VERSION) < 0) Py_CLEAR(m);
+  return m;
+}

@@ -1,6 +1,7 @@
 """The native marshalling accepts exactly the plain calls: what it does not accept goes to the Python binding,
 whose errors are unchanged, and what it accepts gives the binding's results on the binding's stream."""
 import ctypes
+import types
 
 import pytest
 import torch
@@ -198,6 +199,41 @@ def test_capture_takes_the_current_stream():
         torch.cuda.synchronize()
         for n in ("scores", "sel", "cnt", "out", "lse", "smap", "pool_k"):
             assert torch.equal(t[n], ref[n]), n
+
+
+@pytest.fixture
+def fresh_binding():
+    """The binding as before its first call; restored afterwards."""
+    keep = L._lib, L._fast
+    L._lib = L._fast = None
+    yield
+    L._lib, L._fast = keep
+
+
+def _missing():
+    raise ImportError("no module named _fastcall")
+
+
+@pytest.mark.parametrize("load,reason", [
+    (_missing, "no module named"),
+    (lambda: types.SimpleNamespace(__file__="old.so", bind=None), "abi_version"),  # built before it had a version
+    (lambda: types.SimpleNamespace(__file__="old.so", bind=None, abi_version=L.ABI_VERSION - 1), "ABI version"),
+])
+def test_binding_works_without_a_fitting_module(fresh_binding, monkeypatch, load, reason):
+    """The library alone is enough: the calls take the Python binding, and loading says so once."""
+    monkeypatch.setattr(L, "_load_fast", load)
+    with pytest.warns(RuntimeWarning, match=reason):
+        L.lib()
+    assert L._fast is None and P.oasis_abi_version() == L.ABI_VERSION
+    t = _tensors("cpu")
+    with pytest.raises(ValueError, match="scores must be a device tensor"):
+        P.oasis_select_topk(t["d"], t["scores"], t["ctx"], K, t["sel"], t["cnt"], 0)
+
+
+def test_built_module_fits_the_library(fresh_binding, recwarn):
+    L.lib()
+    assert L._fast is not None and L._fast.abi_version == L.ABI_VERSION
+    assert not [w for w in recwarn if "marshalling" in str(w.message)]
 
 
 def test_module_has_no_thread_local_storage():
