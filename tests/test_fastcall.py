@@ -236,6 +236,28 @@ def test_built_module_fits_the_library(fresh_binding, recwarn):
     assert not [w for w in recwarn if "marshalling" in str(w.message)]
 
 
+def test_library_is_built_without_a_host_compiler(monkeypatch, tmp_path):
+    """What fails is the module alone; the library is in place and no older module stays beside it."""
+    from paper_2608_08097_amd import build_lib as b
+    monkeypatch.setattr(b, "LIB_PATH", str(tmp_path / "liboasis.so"))
+    monkeypatch.setattr(b, "FASTCALL_PATH", str(tmp_path / "_fastcall.so"))
+    monkeypatch.setattr(b, "BUILD_DIR", str(tmp_path / "objs"))
+    (tmp_path / "_fastcall.so").write_text("older")
+    monkeypatch.setenv("CXX", str(tmp_path / "no-such-compiler"))
+    run = b._run
+
+    def fake(cmd):  # hipcc's part stands in for itself
+        if cmd[0] != b.hipcc():
+            return run(cmd)
+        open(cmd[cmd.index("-o") + 1], "w").close()
+        return ""
+
+    monkeypatch.setattr(b, "_run", fake)
+    with pytest.warns(RuntimeWarning, match="native marshalling was not built"):
+        assert b.build() == str(tmp_path / "liboasis.so")
+    assert (tmp_path / "liboasis.so").exists() and not (tmp_path / "_fastcall.so").exists()
+
+
 def test_module_has_no_thread_local_storage():
     """Loading a module with a TLS segment slows every thread_local access of the libraries loaded before it."""
     import struct
