@@ -87,3 +87,52 @@ def test_short_contexts_in_long_tables_cost_little_more(Hq, T):
         out[name] = _time_us(lambda: P.oasis_score_blocks(d, q, T, 1, T - 1, mx, mn, ctx, s))
     note(f"scores: fitting table {out['fit']:.1f} us, long table {out['long']:.1f} us")
     assert out["long"] <= 2.7 * out["fit"]
+
+
+def _summaries(pages, table, ctx, NB, block):
+    R, H = table.shape[0], pages.shape[1]
+    out = [torch.zeros((R, H, NB, D), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    d = P.dims(R, H, H, D, block, NB)
+    return out, lambda: P.oasis_build_summaries(d, pages, table, ctx, *out)
+
+
+# the plain form alone, and one request long enough for the non-temporal form beside short ones
+@pytest.mark.parametrize("block,n_cand", [(16, [0, 1, 40, 300]), (32, [5, 0, 150]), (16, [2100, 3, 700, 0]),
+                                          (32, [1100, 2, 333])])
+def test_summaries_do_not_depend_on_the_table_length(block, n_cand):
+    R, H, long = len(n_cand), 8, 4000
+    g = torch.Generator(device="cuda").manual_seed(block + R)
+    NB = max(n_cand) + 1
+    pages = torch.randn((R * NB, H, block, D), generator=g, device="cuda", dtype=torch.bfloat16)
+    perm = torch.randperm(R * NB, generator=g, device="cuda").to(torch.int32).view(R, NB)
+    ctx = torch.tensor([block * n + 1 for n in n_cand], dtype=torch.int32, device="cuda")
+    for nb in (NB, long):
+        table = torch.full((R, nb), -1, dtype=torch.int32, device="cuda")
+        table[:, :NB] = perm
+        note(f"summaries B={block} candidates={n_cand} table={nb}")
+        (kmax, kmin), call = _summaries(pages, table, ctx, nb, block)
+        call()
+        torch.cuda.synchronize()
+        for r, n in enumerate(n_cand):
+            keys = pages[perm[r, :n].long()]
+            for got, ext in ((kmax, keys.amax(2) if n else None), (kmin, keys.amin(2) if n else None)):
+                assert not got[r, :, n:].any()
+                assert n == 0 or torch.equal(got[r, :, :n], ext.transpose(0, 1))
+
+
+def test_short_summaries_in_long_tables_cost_little_more():
+    """75 MB of keys, found in the cache: the table's length adds workgroups that end at once, and does not change
+    how the keys are read. Measured: 14.5 against 15.6 us (1.06 to 1.08 times); read past the caches 19.3 (1.34)."""
+    block = 32
+    R, H, tokens, long = 16, 8, 2304, 96000 // block
+    n = tokens // block
+    pages = torch.randn((R * n, H, block, D), device="cuda", dtype=torch.bfloat16)
+    ctx = torch.full((R,), tokens - 3, dtype=torch.int32, device="cuda")
+    out = {}
+    for name, nb in (("fit", n), ("long", long)):
+        table = torch.full((R, nb), -1, dtype=torch.int32, device="cuda")
+        table[:, :n] = torch.arange(R * n, dtype=torch.int32, device="cuda").view(R, n)
+        note(f"time of summaries B={block} table={nb}")
+        out[name] = _time_us(_summaries(pages, table, ctx, nb, block)[1])
+    note(f"summaries: fitting table {out['fit']:.1f} us, long table {out['long']:.1f} us")
+    assert out["long"] <= 1.2 * out["fit"]
