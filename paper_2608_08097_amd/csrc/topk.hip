@@ -17,8 +17,16 @@ constexpr int kThreads = 1024;
 constexpr int kShortThreads = 512;
 constexpr int kShortKeys = 4;
 
+// Two 1,024-thread workgroups share a CU only if eight waves fit each SIMD: at
+// most 64 VGPRs, and 80 SGPRs of the SIMD's 800 (rounded up to 16, beside 16 of
+// the trap handler). The ballot masks alone take more with 8 keys per thread and
+// up, and 512 rows then ran in two rounds. Measured on MI355X, 512 rows, k = 128,
+// without and with the bound of eight waves (256 rows beside it): 4,096 blocks
+// 15.2 and 10.6 us (7.9), 8,192 blocks 19.8 and 16.3 us (11.3).
+constexpr int kTwoPerCu = 16;  // keys per thread up to which the registers fit
+
 template <int NTHR, int KPT>
-__global__ __launch_bounds__(NTHR) void topk_kernel(TopkArgs a) {
+__global__ __launch_bounds__(NTHR, KPT <= kTwoPerCu ? 8 : 4) void topk_kernel(TopkArgs a) {
   __shared__ SelectShared<NTHR, KPT> sh;
   const int rh = blockIdx.x;
   const int r = rh / a.Hkv;
@@ -36,6 +44,8 @@ hipError_t launch_topk(const TopkArgs& a, hipStream_t s, const LaunchTiming& t) 
   const dim3 grid((unsigned)(a.R * a.Hkv));
   if (a.NBmax <= kShortThreads * kShortKeys)
     launch_kernel(topk_kernel<kShortThreads, kShortKeys>, grid, dim3(kShortThreads), s, t, a);
+  else if (per <= 4)  // (rows of 2,100 to 4,096 blocks: 8 keys 5 to 10 % slower)
+    launch_kernel(topk_kernel<kThreads, 4>, grid, dim3(kThreads), s, t, a);
   else if (per <= 8)
     launch_kernel(topk_kernel<kThreads, 8>, grid, dim3(kThreads), s, t, a);
   else if (per <= 16)
