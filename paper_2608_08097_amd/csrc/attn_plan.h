@@ -43,12 +43,16 @@ inline AttnPlan attn_plan(int R, int Hq, int Hkv, int T, int B, int k_slots, int
   long long want = (kTargetWorkgroups + nrh - 1) / (nrh > 0 ? nrh : 1);
   split(want, kW);
   p.bytes = p.nsplit > 1 ? (std::size_t)nrh * p.nsplit * p.rows * (kHeadDim + 2) * sizeof(float) : 0;
-  // The split launched is the largest that needs no second round of workgroups:
-  // a CU holds one workgroup (of up to two row tiles: one wave per SIMD), so a
-  // few workgroups more than CUs take a round of their own. Measured on MI355X
-  // (8 KV heads, 20 rows, budget 2,048), smallest split that fills against this
-  // one: 3 requests 17.3 against 12.8 us, 5 requests 18.1 and 13.0, 17 requests
-  // 43.0 and 33.6, 22 requests (two splits against one, no merge) 46.3 and 35.5.
+  // The split launched is the largest with at most one workgroup per CU. Of two
+  // row tiles a CU holds one (264 to 268 registers, one wave per SIMD), so a few
+  // workgroups more take a round of their own. Measured on MI355X (8 KV heads, 20
+  // rows, budget 2,048), smallest split that fills against this one: 3 requests
+  // 17.3 against 12.8 us, 5 requests 18.1 and 13.0, 17 requests 43.0 and 33.6, 22
+  // requests (two splits against one, no merge) 46.3 and 35.5. Of one row tile a
+  // CU holds two (204 to 208 registers), so both splits fit one round, but the
+  // merge and the shorter chains cost more than the second workgroup hides: 8
+  // rows, 17 requests 37.5 and 30.2 us, 22 requests 38.4 and 31.7; 16 rows 38.5
+  // and 30.9, 40.1 and 32.6.
   if (p.nsplit > 1 && nrh * p.nsplit > kTargetWorkgroups) want = kTargetWorkgroups / nrh;
   const int least = p.rows <= kRegisterRows ? kW : 6;
   split(want, least);

@@ -31,7 +31,10 @@ __device__ __forceinline__ u32x4 ldg16(const void* p) { return *reinterpret_cast
 // Calls that read at least this much mark their loads non-temporal where whole
 // cache lines are read by one instruction: the data cannot wait in the 256 MB
 // Infinity Cache for its next use beside anything else, and keeping it there
-// only costs. Measured on MI355X over rotating buffers, plain against
+// only costs. The bytes are those of the buffers' capacity where the host cannot
+// see the lengths (attention: every slot up to the table's blocks, read or free;
+// the vector-ALU scorer: the summary tables); the summaries decide in the kernel.
+// Measured on MI355X over rotating buffers, plain against
 // non-temporal: attention of 136 pairs (144 MB) 31.0 and 25.2 us, of 256 (272 MB)
 // 48.3 and 44.5, of 720 (761 MB) 123 and 114; 96 pairs (102 MB) 23.7 and 22.5,
 // 80 pairs (85 MB) level, 64 pairs (68 MB, found in the cache again) 16.9 and

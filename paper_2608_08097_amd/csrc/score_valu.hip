@@ -15,8 +15,14 @@
 // head_dim, and the maximum over the draft rows is kept in the lane. Lanes past the
 // candidates re-read the last candidate block (a cache hit) and write -inf; a
 // wave past them all only writes (64 requests of 5K-17K tokens in 1,088-block
-// rows, with the selection: 46.2 -> 44.9 us). Large calls read past the caches
-// (kStreamBytes): the same 44.1 -> 39.1 us, 8 x 131,072 tokens 58.3 -> 52.5.
+// rows, with the selection: 46.2 -> 44.9 us). Calls whose summary tables take
+// kStreamBytes read past the caches: the same 44.1 -> 39.1 us, 8 x 131,072 tokens
+// 58.3 -> 52.5. The rule is one on the tables' capacity (the host does not see the
+// lengths). Deciding in the kernel from each request's own length instead gains
+// where short contexts leave the data in the cache (16 requests of 4K-8K tokens in
+// 8,000-block tables, 65 MB: 21.8 -> 20.6 us) and costs where it does not fit
+// beside anything else (24 requests of 8K-16K in 4,096-block tables, 75 MB, 27.8
+// -> 30.3) and 1 % in large calls.
 #include "oasis_internal.h"
 
 namespace oasis {
