@@ -31,6 +31,10 @@ CASES = [
     (14, 43, 24, 6, 9, 16, 12, "random"),    # 258 pairs x 36 rows: many-row kernel, one team per pair
     (15, 65, 64, 8, 7, 32, 5, "random"),     # 520 pairs x 56 rows: more than two per CU
     (16, 1, 16, 1, 3, 16, 130, "random"),    # 48 rows, 66 units: many short splits
+    (17, 33, 56, 8, 7, 16, 9, "random"),     # one team per pair: four row tiles (49 rows), 264 pairs
+    (18, 43, 48, 6, 8, 32, 4, "tail"),       # the same at B = 32, 64 rows, 258 pairs
+    (19, 33, 40, 8, 7, 32, 6, "random"),     # three row tiles at B = 32
+    (20, 257, 2, 1, 17, 16, 66, "islands"),  # 34 units per split: a second slot-map chunk
 ]
 
 
@@ -94,6 +98,37 @@ def test_attn_past_the_caches(R, Hq, T, B, ks):
     P.oasis_sparse_decode_attn(d, q, T, pk, pv, smap, ks, ctx, None, out, lse, ws)
     torch.cuda.synchronize()
     for r in (0, R - 1):
+        bits = [host_bits(x[r:r + 1]) for x in (q, pk, pv)]
+        ref_o, ref_l = O.sparse_attend(bits[0], bits[1], np.ascontiguousarray(np.swapaxes(bits[2], -1, -2)),
+                                       smap[r:r + 1].cpu().numpy(), ctx[r:r + 1].cpu().numpy(), B)
+        assert_attn_close(host_bits(out[r:r + 1]), ref_o)
+        assert_lse_close(lse[r:r + 1].cpu().numpy(), ref_l)
+
+
+@pytest.mark.parametrize("R,Hq,T,B,ks", [(25, 32, 2, 16, 128), (16, 64, 9, 32, 128), (25, 32, 5, 32, 64)])
+def test_attn_past_the_caches_with_free_slots(R, Hq, T, B, ks):
+    """The same forms at one row tile (B = 16), five and two (B = 32), with single free slots, runs of them (units
+    that are never read) and NaN in all of them; first, middle and last request."""
+    Hkv = 8
+    g = torch.Generator(device="cuda").manual_seed(R + T)
+    pk = torch.randn((R, ks + 1, Hkv, B, 128), generator=g, device="cuda", dtype=torch.bfloat16)
+    pv = torch.randn((R, ks + 1, Hkv, 128, B), generator=g, device="cuda", dtype=torch.bfloat16)
+    q = torch.randn((R, T, Hq, 128), generator=g, device="cuda", dtype=torch.bfloat16)
+    at = torch.arange(ks, device="cuda")
+    start = torch.randint(0, ks, (R, Hkv, 1), generator=g, device="cuda")
+    free = (torch.rand((R, Hkv, ks), generator=g, device="cuda") < 0.2) | ((at >= start) & (at < start + ks // 4))
+    smap = torch.where(free, -1, at.expand(R, Hkv, ks)).to(torch.int32).contiguous()
+    for pool in (pk, pv):
+        pool[:, :ks][free.transpose(1, 2)] = float("nan")
+    ctx = torch.randint((ks + 1) * B - B + 1, (ks + 1) * B + 1, (R,), generator=g, device="cuda", dtype=torch.int32)
+    assert pk.numel() * 4 > 96 << 20
+    d = P.dims(R, Hq, Hkv, 128, B, ks + 2)
+    out, lse = torch.empty_like(q), torch.empty((R, T, Hq), device="cuda")
+    ws = torch.zeros(max(1, P.oasis_attn_workspace_bytes(d, T, ks)), dtype=torch.uint8, device="cuda")
+    note(f"attn past the caches, free slots R={R} Hq={Hq} T={T} B={B} ks={ks}")
+    P.oasis_sparse_decode_attn(d, q, T, pk, pv, smap, ks, ctx, None, out, lse, ws)
+    torch.cuda.synchronize()
+    for r in (0, R // 2, R - 1):
         bits = [host_bits(x[r:r + 1]) for x in (q, pk, pv)]
         ref_o, ref_l = O.sparse_attend(bits[0], bits[1], np.ascontiguousarray(np.swapaxes(bits[2], -1, -2)),
                                        smap[r:r + 1].cpu().numpy(), ctx[r:r + 1].cpu().numpy(), B)
