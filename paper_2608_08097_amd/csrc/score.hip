@@ -63,21 +63,32 @@ __global__ __launch_bounds__(256) void score_kernel(ScoreArgs a) {
   // A workgroup past the candidates only writes padding: tables are sized for the
   // longest context, so with short contexts in long tables most workgroups end
   // here. Measured on MI355X, scores and selection, without and with this exit
-  // (8 KV heads): 16 requests of 4K-8K tokens in 8,000-block tables, 16 rows 32.1
-  // and 21.3 us, 64 rows 42.8 and 22.8; 64 requests of 1.5K-2.5K in 2,032-block
-  // tables, 32 rows 37.6 and 24.2. Waiting for the context length before the
-  // first load costs full rows up to 0.8 us (8 x 131,072 tokens, 16 rows: 56.4, 57.1).
-  const int blk0 = group * 4 * TPW * 16;
-  if (blk0 >= c.n_cand) {
+  // (8 KV heads): 16 requests of 4K-8K tokens in 8,000-block tables, 16 rows 32.2
+  // and 21.7 us, 64 rows 43.1 and 22.6; 64 requests of 1.5K-2.5K in 2,032-block
+  // tables, 32 rows 37.9 and 24.3.
+  auto padding = [&]() __attribute__((always_inline)) {
+    const int blk0 = group * 4 * TPW * 16;
+    if (blk0 < c.n_cand) return false;
     const int end = min(blk0 + 4 * TPW * 16, a.NBmax);
     for (int b = blk0 + threadIdx.x; b < end; b += 256) srow[b] = -INFINITY;
-    return;
+    return true;
+  };
+  // One row tile loads its queries before it waits for the context length (full
+  // rows of 8 x 131,072 tokens 56.9 -> 56.0 us); with more there is no difference
+  // in full rows, and the workgroups that end need not read them (64 rows, 16
+  // requests as above: 29.9 -> 22.6).
+  if constexpr (NRT > 1) {
+    if (padding()) return;
   }
 
   // queries first (cache-resident, needed first), then the summaries of all TPW tiles
   u32x4 qraw[NRT];
 #pragma unroll
   for (int j = 0; j < NRT; ++j) qraw[j] = score_q_raw(a, r, h, threadIdx.x + j * 256);
+  if constexpr (NRT == 1) {
+    asm volatile("" ::: "memory");  // the loads stay before the exit
+    if (padding()) return;
+  }
   const long long sum_base = (long long)rh * a.NBmax * kHeadDim;
   const uint16_t* kmx = a.kmax + sum_base;
   const uint16_t* kmn = a.kmin + sum_base;
